@@ -260,11 +260,10 @@ __global__ __launch_bounds__(256) void gemm_persistent(const GemmParams p, const
         });
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void gemm_staged(const GemmParams p)
+template <typename S>
+__global__ __launch_bounds__(256, 2) void gemm_staged(const GemmParams p)
 {
     const persp::Workgroup wgp = persp::Grid::at_kernel_entry().workgroup();
-    using S = wg::Staged<T>;
     __shared__ __attribute__((aligned(1024))) char lds[S::LDS_BYTES];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -277,11 +276,11 @@ __global__ __launch_bounds__(256) void gemm_staged(const GemmParams p)
 
     typename S::tile_t acc;
     acc.clear();
-    S::run(wgp, acc, a_tile, p.a_sm, p.a_sk, a_rows, p.a_vec != 0, b_tile, p.b_sn, p.b_sk, b_rows, p.b_vec != 0,
-           q.k_begin, q.k_end, lds, wave, lane);
+    S::run(wgp, acc, a_tile, p.a_sm, p.a_sk, a_rows, p.a_sk == 1 ? p.K : p.M, b_tile, p.b_sn, p.b_sk, b_rows,
+           p.b_sk == 1 ? p.K : p.N, q.k_begin, q.k_end, p.K, lds, wave, lane);
 
-    epilogue<typename S::tile_t, S::MT, S::NT>(wgp, p, q, acc, q.m0 + (wave >> 1) * S::WTM,
-                                               q.n0 + (wave & 1) * S::WTN, lds, wave, lane);
+    epilogue<typename S::tile_t, S::MT, S::NT, false, S::PAIRED_N>(wgp, p, q, acc, q.m0 + (wave >> 1) * S::WTM,
+                                                                   q.n0 + (wave & 1) * S::WTN, lds, wave, lane);
 }
 
 // One thread per group of four consecutive n.  Slices are added in order
@@ -361,15 +360,23 @@ hipError_t launch_persistent(int ab_dtype, const GemmParams& p, int total, int w
     return hipGetLastError();
 }
 
+template <typename T>
+static hipError_t launch_staged_typed(const GemmParams& p, int workgroups, hipStream_t stream)
+{
+    const dim3 grid(workgroups), block(256);
+    const bool a_mk = p.a_sk != 1, b_kn = p.b_sk != 1;  // contiguous along m / n and not along k
+    if (a_mk && b_kn) hipLaunchKernelGGL((gemm_staged<wg::Staged<T, 128, 128, true, true>>), grid, block, 0, stream, p);
+    else if (a_mk) hipLaunchKernelGGL((gemm_staged<wg::Staged<T, 128, 128, true, false>>), grid, block, 0, stream, p);
+    else if (b_kn) hipLaunchKernelGGL((gemm_staged<wg::Staged<T, 128, 128, false, true>>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((gemm_staged<wg::Staged<T, 128, 128, false, false>>), grid, block, 0, stream, p);
+    return hipGetLastError();
+}
+
 hipError_t launch_staged(int ab_dtype, const GemmParams& p, int workgroups, hipStream_t stream)
 {
-    if (ab_dtype == DT_BF16)
-        hipLaunchKernelGGL(gemm_staged<bf16_t>, dim3(workgroups), dim3(256), 0, stream, p);
-    else if (ab_dtype == DT_F16)
-        hipLaunchKernelGGL(gemm_staged<f16_t>, dim3(workgroups), dim3(256), 0, stream, p);
-    else
-        hipLaunchKernelGGL(gemm_staged<f32_t>, dim3(workgroups), dim3(256), 0, stream, p);
-    return hipGetLastError();
+    if (ab_dtype == DT_BF16) return launch_staged_typed<bf16_t>(p, workgroups, stream);
+    if (ab_dtype == DT_F16) return launch_staged_typed<f16_t>(p, workgroups, stream);
+    return launch_staged_typed<f32_t>(p, workgroups, stream);
 }
 
 hipError_t launch_reduce(const GemmParams& p, hipStream_t stream)

@@ -775,162 +775,304 @@ struct PersistentPipe {
 };
 
 // ------------------------------------------------------------------------------------
-// Staged main loop: any element strides and alignments, 16-bit or fp32 operands.  The
-// operands of a K step pass through registers, are zero-filled outside the matrix and
-// written to one LDS slot; the loads of step t+1 are in flight while step t computes.
-// A K step is 128 bytes of every operand row (64 elements of a 16-bit type, 32 of fp32).
-// This is the paper's sgemm structure (section 6.1: block tile staged in shared memory,
-// then warp- and thread-level tiles), with the thread-level tile replaced by MFMA blocks.
+// Staged main loop: any sizes, pitches and alignments, 16-bit or fp32 operands.  The operands
+// of a K step pass through registers on their way to LDS, because a direct-to-LDS copy needs
+// whole aligned 16-byte chunks and a register load does not: the vector memory unit takes a
+// 16-byte load from any element boundary.  A K step is 128 bytes of every operand row (64
+// elements of a 16-bit type, 32 of fp32).
+//
+// An operand keeps the shape it has in memory: K-contiguous rows become the 128-byte rows of
+// TileLayout, an operand contiguous along its other index becomes k-rows whose fragments come
+// from the transposing reads (wave::read_k_rows_half; fp32: four 4-byte reads).  Either way a
+// thread moves whole 16-byte chunks.
+//
+// What bounds it: the time from a load to its use, at one or two workgroups per compute unit.
+// So two K steps are in flight in registers beside the two in LDS (a load issued in step t is
+// written to LDS in step t + 2 and used in step t + 3), and a step has one barrier.  Measured:
+// 1999 x 2001 x 1003 bf16, odd pitches, 24.2 us (131.8 us with element loads for every unaligned
+// chunk and one LDS slot); 960 x 3072 x 3733, row-major B, 53 us (329).
+//
+// Only the last K step can hold k beyond the matrix or read past an operand's last element.  It
+// is computed first and takes the careful fetch: chunks are loaded from where they lie wholly inside their row and
+// moved into place in registers, zeros behind.  All other steps are loads at a uniform base plus
+// fixed per-lane offsets: rows beyond the matrix re-read its last row, and a chunk that
+// straddles the end of a k-row brings elements of the next one, which only feed results that
+// are never stored.
+// This is the paper's sgemm structure (section 6.1: block tile staged in shared memory, then
+// warp- and thread-level tiles), with the thread-level tile replaced by MFMA blocks.
 // ------------------------------------------------------------------------------------
-template <typename T>
-struct Staged {
+using u32x4_any = __attribute__((ext_vector_type(4), aligned(2))) uint32_t;  // 16 bytes at an element boundary
+
+using global_bytes = const __attribute__((address_space(1))) char*;
+
+// The 16 bytes of v moved down by `bytes` (0 .. 16 and more), zeros behind them.
+__device__ __forceinline__ u32x4 chunk_moved_down(u32x4 v, uint32_t bytes)
+{
+    const uint32_t b = bytes & 3;
+    uint32_t w0 = __builtin_amdgcn_alignbyte(v[1], v[0], b), w1 = __builtin_amdgcn_alignbyte(v[2], v[1], b);
+    uint32_t w2 = __builtin_amdgcn_alignbyte(v[3], v[2], b), w3 = __builtin_amdgcn_alignbyte(0u, v[3], b);
+    if (bytes & 4) { w0 = w1; w1 = w2; w2 = w3; w3 = 0u; }
+    if (bytes & 8) { w0 = w2; w1 = w3; w2 = 0u; w3 = 0u; }
+    return bytes < 16 ? u32x4{w0, w1, w2, w3} : u32x4{0u, 0u, 0u, 0u};
+}
+
+// One operand of the staged loop: EXT rows (m or n) of a tile, K-contiguous or (K_ROWS) as
+// k-rows.  DEAL_PAIRED: the rows are dealt to LDS in the paired order (lane::paired_tile_row).
+template <typename T, int EXT, bool K_ROWS, bool DEAL_PAIRED, int THREADS>
+struct StagedOperand {
     using L = lane::TileLayout<64>;  // rows of 128 bytes
-    static constexpr int ES = Frag<T>::kElemBytes, EPC = lane::kChunkBytes / ES;  // elements per chunk
-    static constexpr int BM = 128, BN = 128, BK = L::kRowBytes / ES, NW = 4, THREADS = 256;
-    static constexpr int WTM = 64, WTN = 64, MT = WTM / lane::kBlock, NT = WTN / lane::kBlock;
+    static constexpr int ES = Frag<T>::kElemBytes, EPC = lane::kChunkBytes / ES;
+    static constexpr int BK = L::kRowBytes / ES;
+    static constexpr int CHUNKS = EXT * L::kChunksPerRow / THREADS;   // per thread
+    static constexpr int ROW_BYTES = K_ROWS ? EXT * ES : L::kRowBytes, PER_ROW = ROW_BYTES / lane::kChunkBytes;
+    static constexpr int ROW_STEP = THREADS / PER_ROW;                // LDS rows between a thread's chunks
+    static constexpr int BYTES = EXT * L::kRowBytes;
+    static_assert(ROW_STEP % 8 == 0 && EXT % ROW_STEP == 0, "the swizzle of a thread's chunks must not depend on their number");
+    static_assert(!K_ROWS || !DEAL_PAIRED, "k-rows lie in LDS as in memory");
+
+    const char* tile;   // element (first row of the tile, k 0)
+    int64_t pitch;      // bytes between rows, or between k-rows
+    int rows;           // rows of the tile that exist, >= 1
+    bool narrow;        // the contiguous dimension is shorter than a chunk
+    int row0, chunk;    // this thread's first LDS row and its chunk of every row
+    uint32_t lds_off;
+    uint32_t off[CHUNKS];
+
+    __device__ __forceinline__ int tile_row(int i) const
+    {
+        const int r = row0 + i * ROW_STEP;
+        return DEAL_PAIRED ? lane::paired_tile_row(r) : r;
+    }
+    // s_row / s_k: element strides, one of them 1; extent: elements of the contiguous dimension
+    __device__ __forceinline__ void init(const char* tile_, int64_t s_row, int64_t s_k, int rows_, int64_t extent, int tid)
+    {
+        tile = tile_;
+        pitch = ES * (K_ROWS ? s_k : s_row);
+        rows = rows_;
+        narrow = extent < EPC;
+        row0 = tid / PER_ROW;
+        chunk = tid % PER_ROW;
+        int swz;
+        if constexpr (!K_ROWS) swz = L::swizzle(row0);
+        else if constexpr (ES == 2) swz = (row0 & 3) << 1;
+        else swz = ((row0 >> 2) & 1) << 2;
+        lds_off = row0 * ROW_BYTES + (chunk ^ swz) * lane::kChunkBytes;
+        const int last = (rows - 1) / EPC;
+#pragma unroll
+        for (int i = 0; i < CHUNKS; ++i) {
+            if constexpr (K_ROWS)
+                off[i] = static_cast<uint32_t>((row0 + i * ROW_STEP) * pitch) + (chunk < last ? chunk : last) * lane::kChunkBytes;
+            else {
+                const int r = tile_row(i);
+                off[i] = static_cast<uint32_t>((r < rows ? r : rows - 1) * pitch) + chunk * lane::kChunkBytes;
+            }
+        }
+    }
+    // can a K step inside the matrix be fetched by fixed 32-bit offsets?
+    __device__ __forceinline__ bool regular() const { return !narrow && pitch < (int64_t{1} << 31) / (K_ROWS ? BK : EXT) - 1024; }
+
+    __device__ __forceinline__ void fetch(u32x4 (&regs)[CHUNKS], int k0)
+    {
+        const global_bytes step = (global_bytes)scalarize(tile + (K_ROWS ? k0 * pitch : static_cast<int64_t>(k0) * ES));
+#pragma unroll
+        for (int i = 0; i < CHUNKS; ++i) {
+            // (seen as a fresh 32-bit value, so that the load takes it as its offset register
+            // beside the uniform base instead of a 64-bit sum kept per chunk)
+            asm volatile("" : "+v"(off[i]));
+            regs[i] = *(const __attribute__((address_space(1))) u32x4_any*)(step + off[i]);
+        }
+    }
+    template <bool MAYBE_NARROW>
+    __device__ __forceinline__ void fetch_careful(u32x4 (&regs)[CHUNKS], int k0, int k_end) const
+    {
+        // a chunk's first element, the end of the row it lies in, and that row
+        const int first = K_ROWS ? chunk * EPC : k0 + chunk * EPC, end = K_ROWS ? rows : k_end;
+        auto row = [&](int i) __attribute__((always_inline)) {
+            const int r = tile_row(i);
+            return tile + (K_ROWS ? (k0 + r < k_end ? k0 + r : k_end - 1) : (r < rows ? r : rows - 1)) * pitch;
+        };
+        if (!MAYBE_NARROW || !narrow) {
+            const int from = first + EPC <= end ? first : end - EPC;
+#pragma unroll
+            for (int i = 0; i < CHUNKS; ++i) regs[i] = *reinterpret_cast<const u32x4_any*>(row(i) + static_cast<int64_t>(from) * ES);
+#pragma unroll
+            for (int i = 0; i < CHUNKS; ++i) regs[i] = chunk_moved_down(regs[i], (first - from) * ES);
+        } else {
+#pragma unroll
+            for (int i = 0; i < CHUNKS; ++i) {
+                const char* src = row(i);
+                uint32_t h[EPC];
+#pragma unroll
+                for (int e = 0; e < EPC; ++e) {
+                    const int at = first + e < end ? first + e : end - 1;
+                    if constexpr (ES == 2) h[e] = *reinterpret_cast<const uint16_t*>(src + static_cast<int64_t>(at) * ES);
+                    else h[e] = *reinterpret_cast<const uint32_t*>(src + static_cast<int64_t>(at) * ES);
+                    if (first + e >= end) h[e] = 0u;
+                }
+                if constexpr (ES == 2) regs[i] = u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
+                else regs[i] = u32x4{h[0], h[1], h[2], h[3]};
+                __builtin_amdgcn_sched_barrier(0);  // a chunk at a time: few registers
+            }
+        }
+        if constexpr (K_ROWS) {
+#pragma unroll
+            for (int i = 0; i < CHUNKS; ++i)
+                if (k0 + tile_row(i) >= k_end) regs[i] = u32x4{0u, 0u, 0u, 0u};
+        }
+    }
+    __device__ __forceinline__ void commit(const u32x4 (&regs)[CHUNKS], char* slot) const
+    {
+#pragma unroll
+        for (int i = 0; i < CHUNKS; ++i) *reinterpret_cast<u32x4*>(slot + lds_off + i * ROW_STEP * ROW_BYTES) = regs[i];
+    }
+};
+
+template <typename T, int BM_, int BN_, bool A_MK, bool B_KN>
+struct Staged {
+    using L = lane::TileLayout<64>;
+    static constexpr int ES = Frag<T>::kElemBytes;
+    static constexpr int BM = BM_, BN = BN_, BK = L::kRowBytes / ES, NW = 4, THREADS = 256;
+    static constexpr int WTM = BM / 2, WTN = BN / 2, MT = WTM / lane::kBlock, NT = WTN / lane::kBlock;
     static constexpr int KSUB = L::kChunksPerRow / 4;  // a fragment read covers 4 chunks of a row
-    static constexpr int A_BYTES = BM * L::kRowBytes, B_BYTES = BN * L::kRowBytes;
-    static constexpr int DRAIN_BYTES = NW * drain_patch_bytes(NT);
-    static constexpr int LDS_BYTES = A_BYTES + B_BYTES > DRAIN_BYTES ? A_BYTES + B_BYTES : DRAIN_BYTES;
-    static constexpr int CHUNKS = BM * L::kChunksPerRow / THREADS;  // per thread per operand
+    static constexpr bool PAIRED_N = !B_KN;            // as in Pipeline
+    using A = StagedOperand<T, BM, A_MK, false, THREADS>;
+    using B = StagedOperand<T, BN, B_KN, PAIRED_N, THREADS>;
+    static constexpr int a_slot(int s) { return s * A::BYTES; }
+    static constexpr int b_slot(int s) { return 2 * A::BYTES + s * B::BYTES; }
+    static constexpr int SLOT_BYTES = 2 * (A::BYTES + B::BYTES), DRAIN_BYTES = NW * drain_patch_bytes(NT);
+    static constexpr int LDS_BYTES = SLOT_BYTES > DRAIN_BYTES ? SLOT_BYTES : DRAIN_BYTES;
 
     using tile_t = wave::Tile<T, MT, NT>;
     using frag_t = typename Frag<T>::type;
-    using elem_t = typename std::conditional<ES == 2, uint16_t, uint32_t>::type;
 
-    // One thread's share of a 128-row operand tile as CHUNKS 16-byte chunks.
-    // base: element (row 0 of the tile, k 0 of the matrix); s_row / s_k: element
-    // strides; rows: rows that exist; k0: first k of this step; k_end: end of
-    // the slice.  vec: rows are K-contiguous and every chunk is 16-byte aligned.
-    // With K-contiguous rows consecutive threads take consecutive chunks of a row,
-    // otherwise consecutive rows of one chunk, so that either way they read
-    // neighbouring addresses.
-    __device__ __forceinline__ static void gather(u32x4 (&regs)[CHUNKS], const char* base, int64_t s_row, int64_t s_k,
-                                  int rows, int k0, int k_end, bool vec, int tid)
+    // One operand's fragments of a sub-step: NBLK blocks of 16 rows from row `first` of the tile.
+    template <int EXT, bool K_ROWS, int NBLK>
+    __device__ __forceinline__ static void read(persp::Wave wv, frag_t (&f)[NBLK], const char* slot, int first, int ks, int lane)
     {
-        const bool k_fast = s_k == 1;
+        constexpr int ROW_BYTES = EXT * ES;
+        if constexpr (!K_ROWS) {
+            wave::load_fragments<T, 64, NBLK>(wv, f, slot, first, ks, lane);
+        } else if constexpr (ES == 2) {
+            // (the lane parts take four blocks of 16, 64 elements, from a multiple of 64: a 32-wide
+            // wave tile in the upper half of such a group starts at the third block)
+            uint32_t part[4];
 #pragma unroll
-        for (int i = 0; i < CHUNKS; ++i) {
-            const int q = tid + THREADS * i;
-            const int row = k_fast ? q / L::kChunksPerRow : q % BM;
-            const int c = k_fast ? q % L::kChunksPerRow : q / BM;
-            const int k = k0 + EPC * c;
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if (row < rows && k < k_end) {
-                const char* src = base + ES * (row * s_row + k * s_k);
-                if (vec && k + EPC <= k_end) {
-                    v = *reinterpret_cast<const u32x4*>(src);
-                } else {
-                    uint32_t h[EPC];
+            for (int jl = 0; jl < 4; ++jl) part[jl] = wave::k_rows_lane_part<ROW_BYTES>(wv, jl, lane);
+            const int group = first & ~63, block = (first & 63) / lane::kBlock;
 #pragma unroll
-                    for (int e = 0; e < EPC; ++e)
-                        h[e] = (k + e < k_end) ? *reinterpret_cast<const elem_t*>(src + ES * e * s_k) : 0u;
-                    if constexpr (ES == 2)
-                        v = u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
-                    else
-                        v = u32x4{h[0], h[1], h[2], h[3]};
-                }
+            for (int j = 0; j < NBLK; ++j) {
+                uint32_t at[4];
+#pragma unroll
+                for (int jl = 0; jl < 4; ++jl) at[jl] = NBLK >= 4 || block == 0 ? part[jl] : part[(jl + 2) & 3];
+                const wave::v4s lo = wave::read_k_rows_half<ROW_BYTES>(wv, slot, group, j, ks, 0, at);
+                const wave::v4s hi = wave::read_k_rows_half<ROW_BYTES>(wv, slot, group, j, ks, 1, at);
+                f[j] = __builtin_bit_cast(frag_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
             }
-            regs[i] = v;
-        }
-    }
-
-    // Where one thread's chunks of a whole K step come from, for an operand whose chunks can be
-    // fetched without looking at k: byte offsets from the step's first element (rows beyond the
-    // matrix re-read the last row and are zeroed in commit).  Valid when the operand is
-    // K-contiguous with aligned chunks, or contiguous along its rows.
-    struct Regular {
-        uint32_t off[CHUNKS];
-        bool inside[CHUNKS];
-    };
-    __device__ __forceinline__ static Regular regular(int64_t s_row, int64_t s_k, int rows, int tid)
-    {
-        Regular r;
-        const bool k_fast = s_k == 1;
-#pragma unroll
-        for (int i = 0; i < CHUNKS; ++i) {
-            const int q = tid + THREADS * i;
-            const int row = k_fast ? q / L::kChunksPerRow : q % BM;
-            const int c = k_fast ? q % L::kChunksPerRow : q / BM;
-            r.inside[i] = row < rows;
-            r.off[i] = static_cast<uint32_t>(ES * ((row < rows ? row : rows - 1) * s_row + EPC * c * s_k));
-        }
-        return r;
-    }
-    // All chunks of a K step that lies wholly inside the slice; step0 points at (row 0, first k
-    // of the step).  No address arithmetic per lane: uniform base plus the fixed offsets.
-    __device__ __forceinline__ static void gather_regular(u32x4 (&regs)[CHUNKS], const char* step0, int64_t s_k,
-                                                          const Regular& r)
-    {
-        if (s_k == 1) {
-#pragma unroll
-            for (int i = 0; i < CHUNKS; ++i) regs[i] = *reinterpret_cast<const u32x4*>(step0 + r.off[i]);
         } else {
-            const int64_t pitch = ES * s_k;
+            const int x = lane & 15, g = lane >> 4;
 #pragma unroll
-            for (int i = 0; i < CHUNKS; ++i) {
-                uint32_t h[EPC];
+            for (int j = 0; j < NBLK; ++j) {
+                const int n = first + lane::kBlock * j + x;
+                const char* src = slot + (16 * ks + 4 * g) * ROW_BYTES + (((n >> 2) ^ ((g & 1) << 2)) * lane::kChunkBytes) + (n & 3) * 4;
 #pragma unroll
-                for (int e = 0; e < EPC; ++e) h[e] = *reinterpret_cast<const elem_t*>(step0 + e * pitch + r.off[i]);
-                if constexpr (ES == 2)
-                    regs[i] = u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
-                else
-                    regs[i] = u32x4{h[0], h[1], h[2], h[3]};
+                for (int e = 0; e < 4; ++e) f[j][e] = *reinterpret_cast<const float*>(src + e * ROW_BYTES);
             }
         }
     }
 
-    __device__ __forceinline__ static void commit(const u32x4 (&regs)[CHUNKS], const bool (&inside)[CHUNKS], char* tile,
-                                                  bool k_fast, int tid)
-    {
-#pragma unroll
-        for (int i = 0; i < CHUNKS; ++i) {
-            const int q = tid + THREADS * i;
-            const int row = k_fast ? q / L::kChunksPerRow : q % BM;
-            const int c = k_fast ? q % L::kChunksPerRow : q / BM;
-            *reinterpret_cast<u32x4*>(tile + L::offset(row, c)) = inside[i] ? regs[i] : u32x4{0u, 0u, 0u, 0u};
-        }
-    }
-
-    __device__ __forceinline__ static void run(persp::Workgroup wgp, tile_t& acc, const char* a_tile, int64_t a_sm, int64_t a_sk, int a_rows, bool a_vec,
-                               const char* b_tile, int64_t b_sn, int64_t b_sk, int b_rows, bool b_vec,
-                               int k_begin, int k_end, char* lds, int wave, int lane)
+    // a_tile / b_tile: element (first row of the tile, k 0); a_extent / b_extent: elements of the
+    // operand's contiguous dimension; k_end: end of the slice, a whole number of steps from
+    // k_begin unless it is the end of the matrix (K).
+    __device__ __forceinline__ static void run(persp::Workgroup wgp, tile_t& acc, const char* a_tile, int64_t a_sm, int64_t a_sk, int a_rows,
+                               int a_extent, const char* b_tile, int64_t b_sn, int64_t b_sk, int b_rows, int b_extent,
+                               int k_begin, int k_end, int K, char* lds, int wave, int lane)
     {
         const persp::Wave wv = wgp.wave();  // every wave of the workgroup runs this code
         const int tid = wave * 64 + lane;
-        const int wave_m = wave >> 1, wave_n = wave & 1;
-        // Whole K steps of "regular" operands take the cheap fetch; the last, partial step and
-        // operands with other strides or alignments take the general one.
-        auto is_regular = [](int64_t s_row, int64_t s_k, bool vec) {
-            const int64_t reach = (BM - 1) * (s_row < 0 ? -s_row : s_row) + (BK - 1) * (s_k < 0 ? -s_k : s_k);
-            return (s_k == 1 ? vec : s_row == 1) && s_row >= 0 && s_k >= 0 && reach * ES < (int64_t{1} << 31);
+        const int a_row0 = (wave >> 1) * WTM, b_row0 = (wave & 1) * WTN;
+        A a;
+        B b;
+        a.init(a_tile, a_sm, a_sk, a_rows, a_extent, tid);
+        b.init(b_tile, b_sn, b_sk, b_rows, b_extent, tid);
+        const int steps = (k_end - k_begin + BK - 1) / BK;
+        const bool regular = a.regular() && b.regular() && steps > 1;
+
+        u32x4 ra[2][A::CHUNKS], rb[2][B::CHUNKS];  // two K steps on their way
+        // Step t (past the end: the last whole one again, never used, so that the loop has no
+        // branch around a load and waits for exactly the loads it needs)
+        auto fetch = [&](int t, int set) __attribute__((always_inline)) {
+            const int k0 = k_begin + (t < steps - 2 ? t : steps - 2) * BK;
+            a.fetch(ra[set], k0);
+            b.fetch(rb[set], k0);
         };
-        const bool all_regular = is_regular(a_sm, a_sk, a_vec) && is_regular(b_sn, b_sk, b_vec);
-        const Regular pa = regular(a_sm, a_sk, a_rows, tid), pb = regular(b_sn, b_sk, b_rows, tid);
-        u32x4 ra[CHUNKS], rb[CHUNKS];
-        auto fetch = [&](int k0) __attribute__((always_inline)) {
-            if (all_regular && k0 + BK <= k_end) {
-                gather_regular(ra, a_tile + ES * k0 * a_sk, a_sk, pa);
-                gather_regular(rb, b_tile + ES * k0 * b_sk, b_sk, pb);
-            } else {
-                gather(ra, a_tile, a_sm, a_sk, a_rows, k0, k_end, a_vec, tid);
-                gather(rb, b_tile, b_sn, b_sk, b_rows, k0, k_end, b_vec, tid);
-            }
+        auto commit = [&](int set, int slot) __attribute__((always_inline)) {
+            a.commit(ra[set], lds + a_slot(slot));
+            b.commit(rb[set], lds + b_slot(slot));
         };
-        fetch(k_begin);
-        for (int k0 = k_begin; k0 < k_end; k0 += BK) {
-            sync(wgp);  // the previous step's fragment reads are finished
-            commit(ra, pa.inside, lds, a_sk == 1, tid);
-            commit(rb, pb.inside, lds + A_BYTES, b_sk == 1, tid);
-            sync(wgp);
-            if (k0 + BK < k_end) fetch(k0 + BK);  // next step's operands travel while this one computes
+        auto compute = [&](int slot) __attribute__((always_inline)) {
 #pragma unroll
             for (int ks = 0; ks < KSUB; ++ks) {
                 frag_t fa[MT], fb[NT];
-                wave::load_fragments<T, 64, MT>(wv, fa, lds, wave_m * WTM, ks, lane);
-                wave::load_fragments<T, 64, NT>(wv, fb, lds + A_BYTES, wave_n * WTN, ks, lane);
-                acc.mma(wv, fa, fb);
+                read<BM, A_MK, MT>(wv, fa, lds + a_slot(slot), a_row0, ks, lane);
+                read<BN, B_KN, NT>(wv, fb, lds + b_slot(slot), b_row0, ks, lane);
+#pragma unroll
+                for (int e = 0; e < wave::mfma_parts(frag_t{}); ++e)
+#pragma unroll
+                    for (int i = 0; i < MT; ++i)
+#pragma unroll
+                        for (int j = 0; j < NT; ++j) acc.acc[i][j] = wave::mfma_part(wv, fb[j], fa[i], e, acc.acc[i][j]);
             }
+        };
+        // my LDS reads and writes are done; loads into registers stay in flight across the barrier
+        auto hand_over = [&]() __attribute__((always_inline)) {
+            wait_counts<63, 0>();
+            asm volatile("" ::: "memory");
+            barrier(wgp);
+            asm volatile("" ::: "memory");
+            PRISM_PARANOID_SYNC(wgp);
+        };
+
+        // One step through slot 1 by the careful fetch, nothing ahead of it.
+        u32x4 ca[A::CHUNKS], cb[B::CHUNKS];
+        if (!regular) {
+            for (int k0 = k_begin; k0 < k_end; k0 += BK) {
+                a.template fetch_careful<true>(ca, k0, k_end);
+                b.template fetch_careful<true>(cb, k0, k_end);
+                a.commit(ca, lds + a_slot(1));
+                b.commit(cb, lds + b_slot(1));
+                hand_over();
+                compute(1);
+                hand_over();
+            }
+            return;
+        }
+        // The last step goes first, through slot 1, while the first two travel.
+        fetch(0, 0);
+        fetch(1, 1);
+        a.template fetch_careful<false>(ca, k_begin + (steps - 1) * BK, k_end);
+        b.template fetch_careful<false>(cb, k_begin + (steps - 1) * BK, k_end);
+        a.commit(ca, lds + a_slot(1));
+        b.commit(cb, lds + b_slot(1));
+        commit(0, 0);
+        fetch(2, 0);
+        hand_over();
+        compute(1);
+        hand_over();
+        // Step t computes from slot t % 2 while step t + 1 goes from its registers into the other
+        // slot (everybody left that slot at the last barrier) and step t + 3 sets out into the
+        // registers so freed.  (An odd last step is followed by one that computes nothing: the
+        // loop keeps one way through its loads, so that each wait counts exactly.)
+        auto step = [&](int t, int slot) __attribute__((always_inline)) {
+            commit(slot ^ 1, slot ^ 1);
+            fetch(t + 3, slot ^ 1);
+            __builtin_amdgcn_sched_barrier(0);  // the loads set out before the matrix instructions
+            PRISM_PARANOID_SYNC(wgp);
+            if (slot == 0 || t < steps - 1) compute(slot);
+            hand_over();
+        };
+        for (int t = 0; t < steps - 1; t += 2) {
+            step(t, 0);
+            step(t + 1, 1);
         }
     }
 };
