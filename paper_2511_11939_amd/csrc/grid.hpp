@@ -30,9 +30,6 @@ struct GemmParams {
     int c_dtype;          // DT_*
     int bias_along_m;     // 1 when the problem was transposed on the host
     int a_vec, b_vec;     // operand is K-contiguous with 16-byte aligned rows / chunks
-    int c_vec;            // 4-element groups of C (and of the bias) are vector-aligned
-    int p_vec;            // 4-element groups of the split-K scratch are 16-byte aligned
-    int c_vec8;           // 8-element groups of C (and of the bias) start on 16-byte boundaries
     uint64_t* stamps;     // nullptr, or kStampWords uint64 per workgroup of the main kernel (measurement aid)
 };
 
@@ -106,122 +103,108 @@ __host__ __device__ inline TileCoord schedule(int wg, int tiles_m, int tiles_n, 
 }
 
 // ---- epilogue ------------------------------------------------------------------------
-// Four accumulators of one lane: output row m, columns n0..n0+3.
+// Where a finished accumulator tile goes and what is applied on the way: C of one problem with
+// the scalars and the bias of the call, or one slice's partial sums (fp32, nothing applied).
+struct Target {
+    char* c;             // element (0, 0)
+    int64_t row_bytes;
+    const float* bias;   // or nullptr
+    float alpha, beta;
+    int dtype;           // DT_*
+    bool bias_along_m;
+};
+__device__ __forceinline__ Target target_of(const GemmParams& p, int batch)
+{
+    const int esize = p.c_dtype == DT_F32 ? 4 : 2;
+    return Target{p.C + static_cast<int64_t>(batch) * p.batch_c * esize, p.ldc * esize, p.bias, p.alpha, p.beta, p.c_dtype, p.bias_along_m != 0};
+}
+__device__ __forceinline__ Target partial_of(const GemmParams& p, int batch, int slice)
+{
+    float* slab = p.partial + (static_cast<int64_t>(batch) * p.split_k + slice) * p.M * p.N;
+    return Target{reinterpret_cast<char*>(slab), static_cast<int64_t>(p.N) * 4, nullptr, 1.0f, 0.0f, DT_F32, false};
+}
+
+// Four consecutive results of one row: conversions and memory accesses, at any alignment.  The
+// `some` forms touch only the first `count` of them (fewer than four, at the end of a row).
 template <int OUT>  // DT_BF16 / DT_F16 / DT_F32
-__device__ __forceinline__ void finish4(const GemmParams& p, char* c_problem, int m, int n0, f32x4 v)
-{
-    if (m >= p.M || n0 >= p.N) return;
-    constexpr int esize = OUT == DT_F32 ? 4 : 2;
-    char* dst = c_problem + (static_cast<int64_t>(m) * p.ldc + n0) * esize;
-    const bool full = p.c_vec && (n0 + 3 < p.N);
-    float bias[4] = {0.f, 0.f, 0.f, 0.f};
-    if (p.bias) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            bias[q] = p.bias_along_m ? p.bias[m] : (n0 + q < p.N ? p.bias[n0 + q] : 0.f);
-    }
-    float out[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) out[q] = p.alpha * v[q] + bias[q];
-    if (p.beta != 0.0f) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (n0 + q < p.N) {
-                float old;
-                if constexpr (OUT == DT_F32) old = reinterpret_cast<const float*>(dst)[q];
-                else if constexpr (OUT == DT_BF16) old = lane::from_bf16_bits(reinterpret_cast<const uint16_t*>(dst)[q]);
-                else old = lane::from_f16_bits(reinterpret_cast<const uint16_t*>(dst)[q]);
-                out[q] += p.beta * old;
-            }
-        }
-    }
-    if constexpr (OUT == DT_F32) {
-        if (full) {
-            *reinterpret_cast<f32x4*>(dst) = f32x4{out[0], out[1], out[2], out[3]};
-        } else {
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (n0 + q < p.N) reinterpret_cast<float*>(dst)[q] = out[q];
-        }
-    } else {
-        uint16_t h[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            h[q] = OUT == DT_BF16 ? lane::to_bf16_bits(out[q]) : lane::to_f16_bits(out[q]);
-        if (full) {
-            *reinterpret_cast<u32x2*>(dst) = u32x2{static_cast<uint32_t>(h[0]) | (static_cast<uint32_t>(h[1]) << 16),
-                                                  static_cast<uint32_t>(h[2]) | (static_cast<uint32_t>(h[3]) << 16)};
-        } else {
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (n0 + q < p.N) reinterpret_cast<uint16_t*>(dst)[q] = h[q];
-        }
-    }
-}
-
-// finish4 for the output type named in the descriptor.
-__device__ __forceinline__ void finish4_any(const GemmParams& p, char* c_problem, int m, int n0, f32x4 v)
-{
-    if (p.c_dtype == DT_BF16) finish4<DT_BF16>(p, c_problem, m, n0, v);
-    else if (p.c_dtype == DT_F16) finish4<DT_F16>(p, c_problem, m, n0, v);
-    else finish4<DT_F32>(p, c_problem, m, n0, v);
-}
-
-// Eight consecutive results of one row, no bounds to check and no beta term:
-// scale, add the (pre-loaded) bias, convert, store as one or two 16-byte pieces.
-// With alpha == 1 and a zero bias the arithmetic is exact, so there is no
-// separate path for a plain product.
-template <int OUT, bool BIAS>
-__device__ __forceinline__ void finish_run(char* dst, float alpha, const float (&bias)[8], f32x4 lo, f32x4 hi)
-{
-    float o[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-#pragma unroll
-    for (int q = 0; q < 8; ++q) o[q] = BIAS ? alpha * o[q] + bias[q] : alpha * o[q];
-    if constexpr (OUT == DT_F32) {
-        reinterpret_cast<f32x4*>(dst)[0] = f32x4{o[0], o[1], o[2], o[3]};
-        reinterpret_cast<f32x4*>(dst)[1] = f32x4{o[4], o[5], o[6], o[7]};
-    } else {
-        uint32_t w[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const uint32_t a = OUT == DT_BF16 ? lane::to_bf16_bits(o[2 * q]) : lane::to_f16_bits(o[2 * q]);
-            const uint32_t b = OUT == DT_BF16 ? lane::to_bf16_bits(o[2 * q + 1]) : lane::to_f16_bits(o[2 * q + 1]);
-            w[q] = a | (b << 16);
-        }
-        *reinterpret_cast<u32x4*>(dst) = u32x4{w[0], w[1], w[2], w[3]};
-    }
-}
-
-// The same eight results as the 16 bytes of a 16-bit output type, not yet stored.
-template <int OUT, bool BIAS>
-__device__ __forceinline__ u32x4 pack_run(float alpha, const float (&bias)[8], f32x4 lo, f32x4 hi)
+constexpr int out_bytes() { return OUT == DT_F32 ? 4 : 2; }
+template <int OUT>
+__device__ __forceinline__ u32x2 pack4(f32x4 v)
 {
     static_assert(OUT == DT_BF16 || OUT == DT_F16, "16-bit output types");
-    float o[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    uint32_t w[4];
+    uint32_t h[4];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) o[q] = BIAS ? alpha * o[q] + bias[q] : alpha * o[q];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const uint32_t a = OUT == DT_BF16 ? lane::to_bf16_bits(o[2 * q]) : lane::to_f16_bits(o[2 * q]);
-        const uint32_t b = OUT == DT_BF16 ? lane::to_bf16_bits(o[2 * q + 1]) : lane::to_f16_bits(o[2 * q + 1]);
-        w[q] = a | (b << 16);
-    }
-    return u32x4{w[0], w[1], w[2], w[3]};
+    for (int q = 0; q < 4; ++q) h[q] = OUT == DT_BF16 ? lane::to_bf16_bits(v[q]) : lane::to_f16_bits(v[q]);
+    return u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
 }
-
-// Raw fp32 partial sums of one K slice.
-__device__ __forceinline__ void partial4(const GemmParams& p, float* slab, int m, int n0, f32x4 v)
+template <int OUT>
+__device__ __forceinline__ float decode16(uint32_t h)
 {
-    if (m >= p.M || n0 >= p.N) return;
-    float* dst = slab + static_cast<int64_t>(m) * p.N + n0;
-    if (p.p_vec && (n0 + 3 < p.N)) {
-        *reinterpret_cast<f32x4*>(dst) = v;
+    return OUT == DT_BF16 ? lane::from_bf16_bits(static_cast<uint16_t>(h)) : lane::from_f16_bits(static_cast<uint16_t>(h));
+}
+template <int OUT>
+__device__ __forceinline__ f32x4 load4(const char* src)
+{
+    if constexpr (OUT == DT_F32) {
+        return *reinterpret_cast<const f32x4_any*>(src);
     } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            if (n0 + q < p.N) dst[q] = v[q];
+        const u32x2 w = *reinterpret_cast<const u32x2_any*>(src);
+        return f32x4{decode16<OUT>(w[0] & 0xffffu), decode16<OUT>(w[0] >> 16), decode16<OUT>(w[1] & 0xffffu), decode16<OUT>(w[1] >> 16)};
     }
+}
+template <int OUT>
+__device__ __forceinline__ f32x4 load_some(const char* src, int count)
+{
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+        if (q < count) {
+            if constexpr (OUT == DT_F32) v[q] = reinterpret_cast<const float*>(src)[q];
+            else v[q] = decode16<OUT>(reinterpret_cast<const uint16_t*>(src)[q]);
+        }
+    return v;
+}
+template <int OUT>
+__device__ __forceinline__ void store4(char* dst, f32x4 v)
+{
+    if constexpr (OUT == DT_F32) *reinterpret_cast<f32x4_any*>(dst) = v;
+    else *reinterpret_cast<u32x2_any*>(dst) = pack4<OUT>(v);
+}
+// The first `count` (1 .. 7) of eight 16-bit results.
+__device__ __forceinline__ void store_some16(char* dst, u32x4 w, int count)
+{
+    if (count & 4) {
+        *reinterpret_cast<u32x2_any*>(dst) = u32x2{w[0], w[1]};
+        w = u32x4{w[2], w[3], 0u, 0u};
+        dst += 8;
+    }
+    if (count & 2) {
+        reinterpret_cast<uint16_t*>(dst)[0] = static_cast<uint16_t>(w[0]);
+        reinterpret_cast<uint16_t*>(dst)[1] = static_cast<uint16_t>(w[0] >> 16);
+        w[0] = w[1];
+        dst += 4;
+    }
+    if (count & 1) *reinterpret_cast<uint16_t*>(dst) = static_cast<uint16_t>(w[0]);
+}
+template <int OUT>
+__device__ __forceinline__ void store_some(char* dst, f32x4 v, int count)
+{
+    if constexpr (OUT == DT_F32) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+            if (q < count) reinterpret_cast<float*>(dst)[q] = v[q];
+    } else if (count > 0) {
+        const u32x2 w = pack4<OUT>(v);
+        store_some16(dst, u32x4{w[0], w[1], 0u, 0u}, count);
+    }
+}
+__device__ __forceinline__ f32x4 scaled(float alpha, f32x4 v)
+{
+    return f32x4{alpha * v[0], alpha * v[1], alpha * v[2], alpha * v[3]};
+}
+__device__ __forceinline__ f32x4 scaled(float alpha, f32x4 v, f32x4 bias)
+{
+    return f32x4{alpha * v[0] + bias[0], alpha * v[1] + bias[1], alpha * v[2] + bias[2], alpha * v[3] + bias[3]};
 }
 
 }  // namespace grid

@@ -164,12 +164,6 @@ prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, in
     const bool a_kfast = p.a_sk == 1, b_kfast = p.b_sk == 1;
     p.a_vec = a_kfast && aligned(p.A, 16) && p.a_sm % epc == 0 && (p.batch == 1 || p.batch_a % epc == 0);
     p.b_vec = b_kfast && aligned(p.B, 16) && p.b_sn % epc == 0 && (p.batch == 1 || p.batch_b % epc == 0);
-    const size_t c_align = 4 * static_cast<size_t>(c_esize);
-    p.c_vec = aligned(p.C, c_align) && p.ldc % 4 == 0 && (p.batch == 1 || p.batch_c % 4 == 0) &&
-              (!p.bias || p.bias_along_m || aligned(p.bias, 4));
-    p.p_vec = p.N % 4 == 0 && aligned(d->workspace, 16);
-    p.c_vec8 = aligned(p.C, 16) && p.ldc % 8 == 0 && (p.batch == 1 || p.batch_c % 8 == 0) &&
-               (!p.bias || aligned(p.bias, 16));
 
     if (K == 0) {  // C <- bias + beta*C: only the epilogue kernel runs
         plan.kernel = 0;

@@ -56,123 +56,162 @@ __device__ __forceinline__ Placement place(const GemmParams& p, int wg)
 // Accumulators of one wave tile -> C or the split-K scratch.
 // OWN_PATCH false: the patches reuse the operand slots; workgroup-collective, every wave
 // must call it (it starts with a barrier that retires the slots).  OWN_PATCH true: `patch`
-// is this wave's private 16-row patch outside the slots; no barrier, 16 rows per pass.
+// is this wave's private patch outside the slots; no barrier.
+//
+// Three forms: plain (the whole wave tile inside C, nothing read back, the bias, if any, along
+// the columns and held in registers), inside (the same with beta or a bias per row) and edge (every access
+// bounded; the pieces that lie wholly in their row still move as vectors).  None asks for an
+// alignment: rows of odd length, where every access used to be a single element, cost what
+// aligned ones do up to the cache lines they straddle.  Measured: 1999 x 2001 x 1003 bf16 24.2 ->
+// 21.7 us, 128 x 791 x 128 fp32 with beta 28.4 -> 17.8 us; with a row-major B, whose tile no longer
+// drains fp32 values through LDS, 8192 x 4096 x 4096 bf16 255 -> 232 us; 4096 x 4096 x 8192 with fp32
+// C and beta = 1 300 -> 278 us.
 template <typename TileT, int MT, int NT, bool OWN_PATCH = false, bool PAIRED = false>
 __device__ __forceinline__ void epilogue(persp::Workgroup wgp, const GemmParams& p, const Placement& q, const TileT& acc,
                                          int m_wave, int n_wave, char* lds, int wave, int lane)
 {
     const persp::Wave wv = wgp.wave();
-    const int esize = p.c_dtype == DT_F32 ? 4 : 2;
-    char* c_problem = p.C + static_cast<int64_t>(q.batch) * p.batch_c * esize;
+    const grid::Target to = p.split_k > 1 ? grid::partial_of(p, q.batch, q.slice) : grid::target_of(p, q.batch);
     const bool inside = m_wave + lane::kBlock * MT <= p.M && n_wave + lane::kBlock * NT <= p.N;
-    const bool fast = p.split_k == 1 && inside && p.c_vec8 && p.beta == 0.0f && !(p.bias && p.bias_along_m);
-    auto out_type = [&](auto&& run) {
-        if (p.c_dtype == DT_BF16) run(std::integral_constant<int, DT_BF16>{});
-        else if (p.c_dtype == DT_F16) run(std::integral_constant<int, DT_F16>{});
-        else run(std::integral_constant<int, DT_F32>{});
-    };
     char* patch = lds;
     if constexpr (!OWN_PATCH) {
         wg::sync(wgp);  // every wave has finished with the operand slots: they become patches
-        patch = lds + wave * wg::drain_patch_bytes(NT);
+        patch = lds + wave * wg::rows_patch_bytes(NT);
     }
-    if constexpr (PAIRED) {
-        if (fast) {
-            // Common case: whole wave tile inside C, aligned rows, nothing to read back.  Every
-            // lane holds runs of eight consecutive n of row lane % 16 of each block row and
-            // finishes them itself.  A 16-bit result then passes through the patch once, to leave
-            // as whole rows (full cache lines per store instruction, written past the caches'
-            // retention: C is not read again by this kernel); an fp32 result goes straight out.
-            constexpr int RUNS = NT / 2;
-            const int n_lane = n_wave + 8 * (lane >> 4);
-            const int64_t row_bytes = p.ldc * esize;
-            auto run = [&](auto out_c, auto bias_c) {
-                constexpr int OUT = decltype(out_c)::value;
-                constexpr bool BIAS = decltype(bias_c)::value;
-                float bias[BIAS ? RUNS : 1][8];
-                if constexpr (BIAS) {
+    if (m_wave >= p.M || n_wave >= p.N) return;
+    const int64_t row_bytes = to.row_bytes;
+    const int m_lane = m_wave + (lane & 15), n_lane = n_wave + lane::acc_first_col<PAIRED>(0, lane);
+    auto column = [](int j) { return lane::acc_first_col<PAIRED>(j, 0); };  // of block column j, beyond n_lane
+    auto nothing = [](int) {};
+
+    auto plain = [&](auto out_c, auto bias_c) {
+        constexpr int OUT = decltype(out_c)::value, ES = grid::out_bytes<OUT>();
+        constexpr bool BIAS = decltype(bias_c)::value;
+        f32x4 bias[BIAS ? NT : 1];
+        if constexpr (BIAS) {
 #pragma unroll
-                    for (int s = 0; s < RUNS; ++s) {
-                        const f32x4 b0 = *reinterpret_cast<const f32x4*>(p.bias + n_lane + 32 * s);
-                        const f32x4 b1 = *reinterpret_cast<const f32x4*>(p.bias + n_lane + 32 * s + 4);
-                        bias[s][0] = b0[0]; bias[s][1] = b0[1]; bias[s][2] = b0[2]; bias[s][3] = b0[3];
-                        bias[s][4] = b1[0]; bias[s][5] = b1[1]; bias[s][6] = b1[2]; bias[s][7] = b1[3];
-                    }
-                }
-                if constexpr (OUT == DT_F32) {
-                    char* lane_base = c_problem + (m_wave + (lane & 15)) * row_bytes + static_cast<int64_t>(n_lane) * 4;
-                    wg::drain_pairs<MT, NT>(wv, acc, [&](int r_uniform, int c_uniform, f32x4 lo, f32x4 hi) {
-                        grid::finish_run<OUT, BIAS>(lane_base + r_uniform * row_bytes + c_uniform * 4, p.alpha, bias[BIAS ? c_uniform / 32 : 0], lo, hi);
-                    });
-                } else {
-                    char* wave_base = c_problem + m_wave * row_bytes + static_cast<int64_t>(n_wave) * 2;
-                    wg::drain_rows<MT, NT>(
-                        wv, acc, patch, lane,
-                        [&](int r_uniform, int c_uniform, f32x4 lo, f32x4 hi) {
-                                return grid::pack_run<OUT, BIAS>(p.alpha, bias[BIAS ? c_uniform / 32 : 0], lo, hi);
-                        },
-                        [&](int r_uniform, int r_lane, int byte_in_row, u32x4 piece) {
-                            __builtin_nontemporal_store(piece, reinterpret_cast<u32x4*>(wave_base + (r_uniform + r_lane) * row_bytes + byte_in_row));
-                        });
-                }
-            };
-            out_type([&](auto out_c) {
-                if (p.bias) run(out_c, std::true_type{});
-                else run(out_c, std::false_type{});
-            });
-            return;
+            for (int j = 0; j < NT; ++j) bias[j] = *reinterpret_cast<const f32x4_any*>(to.bias + n_lane + column(j));
         }
-    }
-    if constexpr (PAIRED) {
-        if (p.split_k > 1 && inside && p.p_vec) {  // raw partial sums of a K slice, the same way
-            float* slab = p.partial + (static_cast<int64_t>(q.batch) * p.split_k + q.slice) * p.M * p.N;
-            float* lane_base = slab + static_cast<int64_t>(m_wave + (lane & 15)) * p.N + n_wave + 8 * (lane >> 4);
-            wg::drain_pairs<MT, NT>(wv, acc, [&](int r_uniform, int c_uniform, f32x4 lo, f32x4 hi) {
-                float* dst = lane_base + static_cast<int64_t>(r_uniform) * p.N + c_uniform;
-                *reinterpret_cast<f32x4*>(dst) = lo;
-                *reinterpret_cast<f32x4*>(dst + 4) = hi;
+        auto value = [&](int j, f32x4 v) {
+            if constexpr (BIAS) return grid::scaled(to.alpha, v, bias[j]);
+            else return grid::scaled(to.alpha, v);
+        };
+        if constexpr (OUT == DT_F32) {
+            char* lane_base = to.c + m_lane * row_bytes + static_cast<int64_t>(n_lane) * ES;
+            wg::drain_direct<MT, NT>(wv, acc, nothing, [&](int i, int j, f32x4 v) {
+                grid::store4<OUT>(lane_base + lane::kBlock * i * row_bytes + column(j) * ES, value(j, v));
             });
-            return;
+        } else {
+            // streaming stores: C is not read again by this kernel
+            char* wave_base = to.c + m_wave * row_bytes + static_cast<int64_t>(n_wave) * ES;
+            wg::drain_rows<PAIRED, MT, NT>(
+                wv, acc, patch, lane, nothing, [&](int, int j, f32x4 v) { return grid::pack4<OUT>(value(j, v)); },
+                [&](int r_uniform, int r_lane, int byte_in_row, u32x4 piece) {
+                    __builtin_nontemporal_store(piece, reinterpret_cast<u32x4_any*>(wave_base + (r_uniform + r_lane) * row_bytes + byte_in_row));
+                });
         }
-    }
-    auto drain_any = [&](auto&& sink) {
-        if constexpr (OWN_PATCH) wg::drain<MT, NT, 16, 0, PAIRED>(wv, acc, patch, lane, sink);
-        else wg::drain<MT, NT, wg::kDrainRows, 4, PAIRED>(wv, acc, patch, lane, sink);
     };
-    if (p.split_k > 1) {
-        float* slab = p.partial + (static_cast<int64_t>(q.batch) * p.split_k + q.slice) * p.M * p.N;
-        drain_any([&](int r, int c, f32x4 v) { grid::partial4(p, slab, m_wave + r, n_wave + c, v); });
-        return;
-    }
-    if constexpr (!PAIRED) {
-        if (fast) {
-            // Common case for the plain column order: the accumulators pass through the patch and
-            // come back as runs of eight consecutive n.
-            const int n_run = n_wave + 8 * (lane % (2 * NT));
-            float bias[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            if (p.bias) {
-                const f32x4 b0 = *reinterpret_cast<const f32x4*>(p.bias + n_run);
-                const f32x4 b1 = *reinterpret_cast<const f32x4*>(p.bias + n_run + 4);
-                bias[0] = b0[0]; bias[1] = b0[1]; bias[2] = b0[2]; bias[3] = b0[3];
-                bias[4] = b1[0]; bias[5] = b1[1]; bias[6] = b1[2]; bias[7] = b1[3];
+
+    auto general = [&](auto out_c, auto inside_c) {
+        constexpr int OUT = decltype(out_c)::value, ES = grid::out_bytes<OUT>();
+        constexpr bool INSIDE = decltype(inside_c)::value;
+        // Of an edge tile most blocks are wholly inside C or wholly outside, which is the same for
+        // the whole wave; only the others are bounded lane by lane.
+        auto left = [&](int j) { return p.N - (n_lane + column(j)); };  // columns of C from the lane's first one on
+        auto has_row = [&](int i) { return INSIDE || m_lane + lane::kBlock * i < p.M; };
+        auto any_row = [&](int i) { return INSIDE || m_wave + lane::kBlock * i < p.M; };
+        auto all_rows = [&](int i) { return INSIDE || m_wave + lane::kBlock * (i + 1) <= p.M; };
+        constexpr int SPAN = PAIRED ? 32 : lane::kBlock;  // columns that a block (a pair of blocks) covers
+        auto any_column = [&](int j) { return INSIDE || n_wave + column(j) < p.N; };
+        auto all_columns = [&](int j) { return INSIDE || n_wave + (PAIRED ? column(j & ~1) : column(j)) + SPAN <= p.N; };
+        auto load_left = [&](auto type_c, const char* src, int j) __attribute__((always_inline)) {
+            constexpr int TYPE = decltype(type_c)::value;
+            if (all_columns(j)) return grid::load4<TYPE>(src);
+            if (!any_column(j)) return f32x4{0.f, 0.f, 0.f, 0.f};
+            return left(j) >= 4 ? grid::load4<TYPE>(src) : grid::load_some<TYPE>(src, left(j));
+        };
+        // Beside the next tile's fragments, which the persistent kernel holds meanwhile
+        // (OWN_PATCH), there are no registers to fetch anything ahead.
+        constexpr int AHEAD = OWN_PATCH ? 0 : 1;
+        const bool bias_n = to.bias && !to.bias_along_m;
+        auto fetch_bias = [&](int j) __attribute__((always_inline)) {
+            return load_left(std::integral_constant<int, DT_F32>{}, reinterpret_cast<const char*>(to.bias + n_lane + column(j)), j);
+        };
+        f32x4 bias[AHEAD ? NT : 1];
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j) bias[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (bias_n) {
+#pragma unroll
+                for (int j = 0; j < NT; ++j) bias[j] = fetch_bias(j);
             }
-            // the bias must be in registers before the first store is issued: stores and loads
-            // share one in-order counter, so a later wait for the bias would wait for stores too
-            wg::wait_counts<0, 15>();
-            const int64_t row_bytes = p.ldc * esize;
-            char* lane_base = c_problem + m_wave * row_bytes + static_cast<int64_t>(n_run) * esize;
-            out_type([&](auto out_c) {
-                constexpr int OUT = decltype(out_c)::value;
-                auto sink = [&](int r_uniform, int r_lane, f32x4 lo, f32x4 hi) {
-                    grid::finish_run<OUT, true>(lane_base + (r_uniform + r_lane) * row_bytes, p.alpha, bias, lo, hi);
-                };
-                if constexpr (OWN_PATCH) wg::drain_runs16<MT, NT>(wv, acc, patch, lane, sink);
-                else wg::drain_runs<MT, NT>(wv, acc, patch, lane, sink);
-            });
-            return;
         }
-    }
-    drain_any([&](int r, int c, f32x4 v) { grid::finish4_any(p, c_problem, m_wave + r, n_wave + c, v); });
+        char* lane_base = to.c + m_lane * row_bytes + static_cast<int64_t>(n_lane) * ES;
+        // What C holds is fetched one block row ahead, so that its way from memory is covered by
+        // the stores of the row before.
+        f32x4 old[1 + AHEAD][NT];
+        float bias_m[1 + AHEAD] = {};
+        auto fetch = [&](int i) __attribute__((always_inline)) {
+            if (to.beta != 0.0f && has_row(i)) {
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    old[i & AHEAD][j] = load_left(out_c, lane_base + lane::kBlock * i * row_bytes + column(j) * ES, j);
+            }
+            if (to.bias && to.bias_along_m && has_row(i)) bias_m[i & AHEAD] = to.bias[m_lane + lane::kBlock * i];
+        };
+        auto row = [&](int i) __attribute__((always_inline)) {
+            if (i == 0 || !AHEAD) fetch(i);
+            if (AHEAD && i + 1 < MT) fetch(i + 1);
+        };
+        auto value = [&](int i, int j, f32x4 v) __attribute__((always_inline)) {
+            f32x4 add = {0.f, 0.f, 0.f, 0.f};
+            if constexpr (AHEAD) add = bias[j];
+            else if (bias_n) add = fetch_bias(j);
+            const float bm = bias_m[i & AHEAD];
+            if (to.bias_along_m) add = f32x4{bm, bm, bm, bm};
+            f32x4 r = grid::scaled(to.alpha, v, add);
+            if (to.beta != 0.0f) r = grid::scaled(to.beta, old[i & AHEAD][j], r);
+            return r;
+        };
+        if constexpr (OUT == DT_F32) {
+            wg::drain_direct<MT, NT>(wv, acc, row, [&](int i, int j, f32x4 v) {
+                if (!any_row(i) || !any_column(j)) return;
+                char* dst = lane_base + lane::kBlock * i * row_bytes + column(j) * ES;
+                v = value(i, j, v);
+                if (all_rows(i) && all_columns(j)) grid::store4<OUT>(dst, v);
+                else if (has_row(i)) {
+                    if (left(j) >= 4) grid::store4<OUT>(dst, v);
+                    else grid::store_some<OUT>(dst, v, left(j));
+                }
+            });
+        } else {
+            char* wave_base = to.c + m_wave * row_bytes + static_cast<int64_t>(n_wave) * ES;
+            wg::drain_rows<PAIRED, MT, NT>(
+                wv, acc, patch, lane, row, [&](int i, int j, f32x4 v) { return grid::pack4<OUT>(value(i, j, v)); },
+                [&](int r_uniform, int r_lane, int byte_in_row, u32x4 piece) {
+                    const int i = r_uniform / lane::kBlock;
+                    if (!any_row(i)) return;
+                    char* dst = wave_base + (r_uniform + r_lane) * row_bytes + byte_in_row;
+                    const int count = p.N - n_wave - byte_in_row / ES;
+                    if ((all_rows(i) || m_wave + r_uniform + r_lane < p.M)) {
+                        if (INSIDE || count >= 8) __builtin_nontemporal_store(piece, reinterpret_cast<u32x4_any*>(dst));
+                        else if (count > 0) grid::store_some16(dst, piece, count);
+                    }
+                });
+        }
+    };
+
+    auto out_type = [&](auto&& run) {
+        if (to.dtype == DT_BF16) run(std::integral_constant<int, DT_BF16>{});
+        else if (to.dtype == DT_F16) run(std::integral_constant<int, DT_F16>{});
+        else run(std::integral_constant<int, DT_F32>{});
+    };
+    out_type([&](auto out_c) {
+        if (!inside) general(out_c, std::false_type{});
+        else if (to.beta != 0.0f || (to.bias && to.bias_along_m)) general(out_c, std::true_type{});
+        else if (to.bias) plain(out_c, std::true_type{});
+        else plain(out_c, std::false_type{});
+    });
 }
 
 template <typename P, int BM, int BN, int BK, int WAVES_N>
@@ -296,21 +335,29 @@ __global__ __launch_bounds__(256) void splitk_reduce(const GemmParams p)
         const int64_t bm = idx / groups_n;
         const int m = static_cast<int>(bm % p.M);
         const int b = static_cast<int>(bm / p.M);
-        const int n0 = 4 * g;
+        const int n0 = 4 * g, left = p.N - n0;
         f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-        const float* src = p.partial + static_cast<int64_t>(b) * p.split_k * slab + static_cast<int64_t>(m) * p.N + n0;
-        for (int s = 0; s < p.split_k; ++s, src += slab) {
-            if (p.p_vec && n0 + 3 < p.N) {
-                sum += *reinterpret_cast<const f32x4*>(src);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (n0 + e < p.N) sum[e] += src[e];
-            }
-        }
-        const int esize = p.c_dtype == DT_F32 ? 4 : 2;
-        char* c_problem = p.C + static_cast<int64_t>(b) * p.batch_c * esize;
-        grid::finish4_any(p, c_problem, m, n0, sum);
+        const char* src = reinterpret_cast<const char*>(p.partial + static_cast<int64_t>(b) * p.split_k * slab + static_cast<int64_t>(m) * p.N + n0);
+        if (left >= 4)
+            for (int s = 0; s < p.split_k; ++s, src += 4 * slab) sum += grid::load4<DT_F32>(src);
+        else
+            for (int s = 0; s < p.split_k; ++s, src += 4 * slab) sum += grid::load_some<DT_F32>(src, left);
+        const grid::Target to = grid::target_of(p, b);
+        f32x4 add = {0.f, 0.f, 0.f, 0.f};
+        if (to.bias && to.bias_along_m) add = f32x4{to.bias[m], to.bias[m], to.bias[m], to.bias[m]};
+        else if (to.bias && left >= 4) add = grid::load4<DT_F32>(reinterpret_cast<const char*>(to.bias + n0));
+        else if (to.bias) add = grid::load_some<DT_F32>(reinterpret_cast<const char*>(to.bias + n0), left);
+        sum = grid::scaled(to.alpha, sum, add);
+        auto finish = [&](auto out_c) {
+            constexpr int OUT = decltype(out_c)::value;
+            char* dst = to.c + m * to.row_bytes + static_cast<int64_t>(n0) * grid::out_bytes<OUT>();
+            if (to.beta != 0.0f) sum = grid::scaled(to.beta, left >= 4 ? grid::load4<OUT>(dst) : grid::load_some<OUT>(dst, left), sum);
+            if (left >= 4) grid::store4<OUT>(dst, sum);
+            else grid::store_some<OUT>(dst, sum, left);
+        };
+        if (to.dtype == DT_BF16) finish(std::integral_constant<int, DT_BF16>{});
+        else if (to.dtype == DT_F16) finish(std::integral_constant<int, DT_F16>{});
+        else finish(std::integral_constant<int, DT_F32>{});
     }
 }
 

@@ -21,6 +21,12 @@ using f32x4 = __attribute__((ext_vector_type(4))) float;
 using u32x4 = __attribute__((ext_vector_type(4))) uint32_t;
 using u32x2 = __attribute__((ext_vector_type(2))) uint32_t;
 
+// The same vectors at any element boundary: global memory instructions of gfx950 take them there
+// (LDS accesses keep their natural alignment).
+using u32x4_any = __attribute__((ext_vector_type(4), aligned(2))) uint32_t;
+using u32x2_any = __attribute__((ext_vector_type(2), aligned(2))) uint32_t;
+using f32x4_any = __attribute__((ext_vector_type(4), aligned(4))) float;
+
 struct bf16_t {};  // operand tags
 struct f16_t {};
 struct f32_t {};

@@ -82,140 +82,63 @@ __device__ __forceinline__ void copy_async_16(persp::Wave, const char* uniform_b
                  : "memory", "scc");
 }
 
-// Drains one wave's accumulator tile through a private LDS patch so that the
-// values leave the wave as runs of four consecutive n, whole rows at a time
-// (the MFMA leaves each lane with values of 16 different rows).  `patch` must
-// hold kDrainRows x (16*NT + 4) floats, is used by this wave only, and must
-// not be in use by anybody else (barrier before the first call).
-// sink(row_in_wave_tile, col_in_wave_tile, f32x4) receives every group once.
-// This is the general path (any bounds, any alignment); see drain_runs below.
-constexpr int kDrainRows = 32;  // two 16-row blocks per pass
-constexpr int drain_patch_bytes(int nt) { return kDrainRows * (lane::kBlock * nt + 4) * 4; }
-
-// ROWS: rows per pass (32 = two blocks, 16 = one); PAD: floats of row padding (4 keeps the
-// accesses free of bank conflicts, 0 fits 16 rows of a 128-wide tile into 8 KiB).
-template <int MT, int NT, int ROWS = kDrainRows, int PAD = 4, bool PAIRED = false, typename TileT, typename Sink>
-__device__ __forceinline__ void drain(persp::Wave, const TileT& acc, char* patch, int lane, Sink&& sink)
+// ---- from the accumulators to memory ---------------------------------------------------
+// Every lane holds four consecutive columns of one row per block: row 16 i + lane % 16 of the
+// wave tile, columns lane::acc_first_col<PAIRED>(j, lane) and on.  Two ways out:
+//
+// drain_direct (32-bit results): the four values go straight out, 64 contiguous bytes of a row
+// (PAIRED: 128 in two instructions) from the four lanes that share it.
+// row(i) is called before the blocks of block row i, put(i, j, values) for each of them.
+template <int MT, int NT, typename TileT, typename Row, typename Put>
+__device__ __forceinline__ void drain_direct(persp::Wave, const TileT& acc, Row&& row, Put&& put)
 {
-    static_assert(ROWS == 16 || (ROWS == 32 && MT % 2 == 0), "a pass takes one or two 16-row blocks");
-    constexpr int BLOCKS = ROWS / lane::kBlock;
-    constexpr int WTN = lane::kBlock * NT;
-    constexpr int PITCH = WTN + PAD;  // floats
-    constexpr int LANES_PER_ROW = WTN / 4;
-    constexpr int ROWS_PER_ITER = 64 / LANES_PER_ROW > 0 ? 64 / LANES_PER_ROW : 1;
-    constexpr int ITERS = ROWS / ROWS_PER_ITER;
-    static_assert(LANES_PER_ROW <= 64, "one row per wave pass at most");
-    float* buf = reinterpret_cast<float*>(patch);
-#pragma unroll
-    for (int pass = 0; pass < MT / BLOCKS; ++pass) {
-#pragma unroll
-        for (int ii = 0; ii < BLOCKS; ++ii) {
-            float* wr = buf + (lane::kBlock * ii + lane::acc_col(lane)) * PITCH;
-#pragma unroll
-            for (int j = 0; j < NT; ++j)
-                *reinterpret_cast<f32x4*>(wr + lane::acc_first_col<PAIRED>(j, lane)) = acc.acc[BLOCKS * pass + ii][j];
-        }
-        const int col = 4 * (lane % LANES_PER_ROW);
-#pragma unroll 4
-        for (int it = 0; it < ITERS; ++it) {
-            const int row = it * ROWS_PER_ITER + lane / LANES_PER_ROW;
-            const f32x4 v = *reinterpret_cast<const f32x4*>(buf + row * PITCH + col);
-            sink(ROWS * pass + row, col, v);
-        }
-    }
-}
-
-// Fast drain for a wave tile that lies wholly inside C: the accumulators go to
-// the patch as they are (straight from the accumulator registers), come back as
-// runs of eight consecutive n per lane, and sink(row_uniform, row_lane, v_lo, v_hi)
-// finishes and stores each run: row row_uniform + row_lane of the wave tile (the
-// first part is the same for all lanes), columns 8*(lane % (2*NT)) .. +7.
-// Inside a patch row the 16-byte units are stored evens first, odds second, so
-// that both the writes and the two reads of a run are spread over all banks.
-template <int MT, int NT, typename TileT, typename Sink>
-__device__ __forceinline__ void drain_runs(persp::Wave, const TileT& acc, char* patch, int lane, Sink&& sink)
-{
-    static_assert(MT % 2 == 0, "a pass takes two 16-row blocks");
-    constexpr int WTN = lane::kBlock * NT;
-    constexpr int UNITS = WTN / 4;            // 16-byte units per row
-    constexpr int PITCH = (WTN + 4) * 4;      // bytes
-    constexpr int LANES_PER_ROW = WTN / 8;
-    constexpr int ROWS_PER_ITER = 64 / LANES_PER_ROW;
-    constexpr int ITERS = kDrainRows / ROWS_PER_ITER;
-    // unit u of a row sits at position (u >> 1) + (UNITS / 2) * (u & 1)
-    const int run = lane % LANES_PER_ROW, sub = lane / LANES_PER_ROW;
-    // this lane's accumulators of block column j are unit 4j + lane/16 of their row
-    const int q = lane >> 4;
-    const int wr_lane = lane::acc_col(lane) * PITCH + 16 * ((q >> 1) + (UNITS / 2) * (q & 1));
-#pragma unroll
-    for (int pass = 0; pass < MT / 2; ++pass) {
-#pragma unroll
-        for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-            for (int j = 0; j < NT; ++j)
-                *reinterpret_cast<f32x4*>(patch + wr_lane + lane::kBlock * ii * PITCH + 32 * j) = acc.acc[2 * pass + ii][j];
-        f32x4 lo[ITERS], hi[ITERS];
-#pragma unroll
-        for (int it = 0; it < ITERS; ++it) {
-            const char* rd = patch + (it * ROWS_PER_ITER + sub) * PITCH;
-            lo[it] = *reinterpret_cast<const f32x4*>(rd + 16 * run);                 // unit 2*run   -> position run
-            hi[it] = *reinterpret_cast<const f32x4*>(rd + 16 * (run + UNITS / 2));   // unit 2*run+1 -> position run + UNITS/2
-        }
-#pragma unroll
-        for (int it = 0; it < ITERS; ++it) sink(kDrainRows * pass + it * ROWS_PER_ITER, sub, lo[it], hi[it]);
-        __builtin_amdgcn_sched_barrier(0);  // one pass at a time keeps the register need small
-    }
-}
-
-// Drain without LDS for a wave tile whose block columns are paired (lane::paired_tile_row):
-// every lane already holds runs of eight consecutive n.  sink(row_uniform, col_uniform, lo, hi)
-// receives the run of row row_uniform + lane % 16, columns col_uniform + 8 * (lane / 16) .. +7
-// of the wave tile, once for every block row and pair of block columns.
-template <int MT, int NT, typename TileT, typename Sink>
-__device__ __forceinline__ void drain_pairs(persp::Wave, const TileT& acc, Sink&& sink)
-{
-    static_assert(NT % 2 == 0, "block columns come in pairs");
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
+        row(i);
 #pragma unroll
-        for (int s = 0; s < NT / 2; ++s) {
+        for (int j = 0; j < NT; ++j) {
             // (taken from the accumulation registers here and no earlier: without this the moves
             // of all blocks drift to the top of the epilogue and spill)
-            f32x4 lo = acc.acc[i][2 * s], hi = acc.acc[i][2 * s + 1];
-            asm volatile("" : "+a"(lo), "+a"(hi));
-            sink(lane::kBlock * i, 32 * s, lo, hi);
+            f32x4 v = acc.acc[i][j];
+            asm volatile("" : "+a"(v));
+            put(i, j, v);
         }
         __builtin_amdgcn_sched_barrier(0);  // one block row at a time keeps the register need small
     }
 }
 
-// Drain for a 16-bit result of a wave tile with paired block columns.  Every lane finishes its
-// runs of eight consecutive n itself: pack(row_uniform, col_uniform, lo, hi) returns the 16
-// bytes of the run of row row_uniform + lane % 16, columns col_uniform + 8 * (lane / 16) .. +7.
-// The pieces of one block row (16 rows of 32 * NT bytes) pass through the wave's LDS patch and
-// come back row by row, so that store(row_uniform, row_lane, byte_in_row, piece) writes whole
-// rows of the wave tile (16 consecutive lanes hold 256 contiguous bytes).  Four times less LDS
-// traffic than draining the fp32 accumulators, and full cache lines per store instruction.
-// `patch` is this wave's, kRowsPatchBytes(NT) long; the padding of 16 bytes per row spreads
-// both the writes (16 rows, one piece each) and the reads over all banks.
+// drain_rows (16-bit results): pack(i, j, values) returns the four results of a block as 8
+// bytes.  The pieces of one block row (16 rows of 32 * NT bytes) pass through the wave's LDS
+// patch and come back row by row, so that store(row_uniform, row_lane, byte_in_row, piece)
+// writes whole rows of the wave tile (16 consecutive lanes hold 256 contiguous bytes): a
+// quarter of the LDS traffic of draining the fp32 accumulators, and full cache lines per store
+// instruction.  `patch` is this wave's, rows_patch_bytes(NT) long; the padding of 16 bytes per
+// row spreads both the writes (16 rows, one piece each) and the reads over all banks.
 constexpr int rows_patch_bytes(int nt) { return lane::kBlock * (2 * lane::kBlock * nt + 16); }
-template <int MT, int NT, typename TileT, typename Pack, typename Store>
-__device__ __forceinline__ void drain_rows(persp::Wave, const TileT& acc, char* patch, int lane, Pack&& pack, Store&& store)
+template <bool PAIRED, int MT, int NT, typename TileT, typename Row, typename Pack, typename Store>
+__device__ __forceinline__ void drain_rows(persp::Wave, const TileT& acc, char* patch, int lane, Row&& row, Pack&& pack, Store&& store)
 {
     static_assert(NT % 2 == 0, "block columns come in pairs");
     constexpr int ROW_BYTES = 2 * lane::kBlock * NT, PITCH = ROW_BYTES + 16;
     constexpr int PIECES = ROW_BYTES / 16;        // lanes that share a row on the way out
     constexpr int ROWS_PER_ITER = 64 / PIECES, ITERS = lane::kBlock / ROWS_PER_ITER;
-    char* wr = patch + (lane & 15) * PITCH + 16 * (lane >> 4);
+    char* wr = patch + (lane & 15) * PITCH + (PAIRED ? 16 : 8) * (lane >> 4);
     const int piece = lane % PIECES, sub = lane / PIECES;
     const char* rd = patch + sub * PITCH + 16 * piece;
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
+        row(i);
 #pragma unroll
         for (int s = 0; s < NT / 2; ++s) {
             f32x4 lo = acc.acc[i][2 * s], hi = acc.acc[i][2 * s + 1];
             asm volatile("" : "+a"(lo), "+a"(hi));  // taken from the accumulation registers here and no earlier
-            *reinterpret_cast<u32x4*>(wr + 64 * s) = pack(lane::kBlock * i, 32 * s, lo, hi);
+            const u32x2 a = pack(i, 2 * s, lo), b = pack(i, 2 * s + 1, hi);
+            if constexpr (PAIRED) {
+                *reinterpret_cast<u32x4*>(wr + 64 * s) = u32x4{a[0], a[1], b[0], b[1]};
+            } else {
+                *reinterpret_cast<u32x2*>(wr + 64 * s) = a;
+                *reinterpret_cast<u32x2*>(wr + 64 * s + 32) = b;
+            }
         }
         u32x4 out[ITERS];
 #pragma unroll
@@ -266,7 +189,7 @@ struct Pipeline {
     static_assert((NW * COPY_ROWS) % 16 == 0, "the swizzle of a lane's row must not depend on the copy index");
     static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile is made of pairs of 16x16 blocks");
     static_assert(LDS_BYTES <= 163840, "LDS budget of one gfx950 compute unit");
-    static_assert(NW * drain_patch_bytes(NT) <= LDS_BYTES, "epilogue patches reuse the operand slots");
+    static_assert(NW * rows_patch_bytes(NT) <= LDS_BYTES, "epilogue patches reuse the operand slots");
     static_assert(STAGES >= 2 && (STAGES - 1) * COPIES <= 63, "vmcnt range");
 
     using tile_t = wave::Tile<T, MT, NT>;
@@ -539,44 +462,6 @@ struct Pipeline {
     }
 };
 
-// drain_runs with one 16-row block per pass and no padding: the patch is 16 rows of
-// 16*NT floats (8 KiB for a 128-wide wave tile).  Instead of padding, the 16-byte unit at
-// position p of row r is kept at position p ^ r (positions as in drain_runs: even units
-// first), which spreads the 16 rows of a write and the 16 units of a read over the banks.
-template <int MT, int NT, typename TileT, typename Sink>
-__device__ __forceinline__ void drain_runs16(persp::Wave, const TileT& acc, char* patch, int lane, Sink&& sink)
-{
-    constexpr int WTN = lane::kBlock * NT;
-    constexpr int UNITS = WTN / 4;
-    constexpr int PITCH = WTN * 4;            // bytes
-    constexpr int LANES_PER_ROW = WTN / 8;
-    constexpr int ROWS_PER_ITER = 64 / LANES_PER_ROW;
-    constexpr int ITERS = lane::kBlock / ROWS_PER_ITER;
-    static_assert(UNITS / 2 >= 16 || UNITS / 2 == 8, "the row index is folded into the low position bits");
-    constexpr int FOLD = UNITS / 2 >= 16 ? 15 : 7;  // bits of the row folded into the position
-    const int run = lane % LANES_PER_ROW, sub = lane / LANES_PER_ROW;
-    const int q = lane >> 4, r = lane::acc_col(lane);
-    const int pos_q = (q >> 1) + (UNITS / 2) * (q & 1);  // plus 2j for block column j
-    char* wr = patch + r * PITCH;
-#pragma unroll
-    for (int i = 0; i < MT; ++i) {
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-            *reinterpret_cast<f32x4*>(wr + 16 * ((pos_q + 2 * j) ^ (r & FOLD))) = acc.acc[i][j];
-        f32x4 lo[ITERS], hi[ITERS];
-#pragma unroll
-        for (int it = 0; it < ITERS; ++it) {
-            const int row = it * ROWS_PER_ITER + sub;
-            const char* rd = patch + row * PITCH;
-            lo[it] = *reinterpret_cast<const f32x4*>(rd + 16 * (run ^ (row & FOLD)));
-            hi[it] = *reinterpret_cast<const f32x4*>(rd + 16 * ((run + UNITS / 2) ^ (row & FOLD)));
-        }
-#pragma unroll
-        for (int it = 0; it < ITERS; ++it) sink(lane::kBlock * i + it * ROWS_PER_ITER, sub, lo[it], hi[it]);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
 // ------------------------------------------------------------------------------------
 // Persistent form of the pipeline: one workgroup walks a sequence of 256x256 tiles and
 // treats their K steps as one stream.  The copies issued in the last two steps of a tile
@@ -600,7 +485,7 @@ struct PersistentPipe {
     static constexpr int A_BYTES = BM * L::kRowBytes, B_BYTES = BN * L::kRowBytes, STAGE_BYTES = A_BYTES + B_BYTES;
     static constexpr int a_slot(int stage) { return stage * A_BYTES; }              // A tiles of both slots first,
     static constexpr int b_slot(int stage) { return 2 * A_BYTES + stage * B_BYTES; }  // then the B tiles (see Pipeline)
-    static constexpr int PATCH_BYTES = lane::kBlock * WTN * 4;
+    static constexpr int PATCH_BYTES = rows_patch_bytes(NT);
     static constexpr int PATCH_BASE = 2 * STAGE_BYTES;
     static constexpr int LDS_BYTES = PATCH_BASE + NW * PATCH_BYTES;
     static constexpr int COPY_ROWS = 8, A_COPIES = BM / COPY_ROWS / NW, COPIES = 2 * A_COPIES;
@@ -801,8 +686,6 @@ struct PersistentPipe {
 // This is the paper's sgemm structure (section 6.1: block tile staged in shared memory, then
 // warp- and thread-level tiles), with the thread-level tile replaced by MFMA blocks.
 // ------------------------------------------------------------------------------------
-using u32x4_any = __attribute__((ext_vector_type(4), aligned(2))) uint32_t;  // 16 bytes at an element boundary
-
 using global_bytes = const __attribute__((address_space(1))) char*;
 
 // The 16 bytes of v moved down by `bytes` (0 .. 16 and more), zeros behind them.
@@ -939,8 +822,8 @@ struct Staged {
     using B = StagedOperand<T, BN, B_KN, PAIRED_N, THREADS>;
     static constexpr int a_slot(int s) { return s * A::BYTES; }
     static constexpr int b_slot(int s) { return 2 * A::BYTES + s * B::BYTES; }
-    static constexpr int SLOT_BYTES = 2 * (A::BYTES + B::BYTES), DRAIN_BYTES = NW * drain_patch_bytes(NT);
-    static constexpr int LDS_BYTES = SLOT_BYTES > DRAIN_BYTES ? SLOT_BYTES : DRAIN_BYTES;
+    static constexpr int LDS_BYTES = 2 * (A::BYTES + B::BYTES);
+    static_assert(NW * rows_patch_bytes(NT) <= LDS_BYTES, "epilogue patches reuse the operand slots");
 
     using tile_t = wave::Tile<T, MT, NT>;
     using frag_t = typename Frag<T>::type;
