@@ -132,10 +132,9 @@ template <int OUT>
 __device__ __forceinline__ u32x2 pack4(f32x4 v)
 {
     static_assert(OUT == DT_BF16 || OUT == DT_F16, "16-bit output types");
-    uint32_t h[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) h[q] = OUT == DT_BF16 ? lane::to_bf16_bits(v[q]) : lane::to_f16_bits(v[q]);
-    return u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+    // (as vectors: the compiler then has one conversion instruction per pair of bf16)
+    if constexpr (OUT == DT_BF16) return __builtin_bit_cast(u32x2, __builtin_convertvector(v, bf16x4));
+    else return __builtin_bit_cast(u32x2, __builtin_convertvector(v, f16x4));
 }
 template <int OUT>
 __device__ __forceinline__ float decode16(uint32_t h)

@@ -199,8 +199,10 @@ prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, in
             const int64_t big = ceil_div(p.M, 256) * ceil_div(p.N, 256) * batch;
             cfg = (big >= kComputeUnits / 2 || ksteps >= kVeryLongK) ? 0 : 1;
         }
-        // an operand that is not K-contiguous: 128x128 tiles, that operand kept as k-rows in LDS
-        if (!p.a_vec || !p.b_vec) cfg = !p.a_vec ? (!p.b_vec ? 4 : 3) : 2;
+        // an operand that is not K-contiguous is kept as k-rows in LDS, with either tile (the line
+        // is the same: 6656 x 1792 x 640 with 182 large tiles 22.0 -> 19.9 us, 704 x 2368 x 3456 with
+        // 30 stays on small tiles)
+        if (!p.a_vec || !p.b_vec) cfg = (cfg == 0 ? 9 : 2) + (!p.a_vec ? (!p.b_vec ? 2 : 1) : 0);
         // fp32 operands: 128x128 tiles in all four layout pairs
         if (ab_esize == 4) cfg = 5 + (p.b_vec ? 0 : 1) + (p.a_vec ? 0 : 2);
         out->pipe_config = cfg;
@@ -222,7 +224,7 @@ prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, in
         // workgroups per compute unit, so they are split until there are about twice as many
         // workgroups as compute units (measured: 512x512x16384 23 us with 16 slices, 28 with
         // 8 or 32).
-        const bool small_tiles = plan.kernel != 2 || out->pipe_config != 0;
+        const bool small_tiles = tile_m != 256;
         const int64_t slots = small_tiles ? 2 * kComputeUnits : kComputeUnits;
         // (a K step of fp32 operands holds four times the matrix instructions of a 16-bit one)
         const bool short_steps = plan.kernel == 2 && ab_esize == 2;

@@ -23,6 +23,9 @@ const PipeConfig kPipeConfigs[kNumPipeConfigs] = {
     {6, 128, 128, 32, 4, 2, "f32_128x128x32_w4_b_along_n"},
     {7, 128, 128, 32, 4, 2, "f32_128x128x32_w4_a_along_m"},
     {8, 128, 128, 32, 4, 2, "f32_128x128x32_w4_a_along_m_b_along_n"},
+    {9, 256, 256, 64, 4, 2, "256x256x64_w4_b_along_n"},
+    {10, 256, 256, 64, 4, 2, "256x256x64_w4_a_along_m"},
+    {11, 256, 256, 64, 4, 2, "256x256x64_w4_a_along_m_b_along_n"},
 };
 
 namespace {
@@ -377,6 +380,9 @@ hipError_t launch_pipe_config(int config, const GemmParams& p, int workgroups, h
     case 2: return launch_pipe<wg::Pipeline<T, 128, 128, 64, 2, 2, 2, true>, 128, 128, 64, 2>(p, workgroups, stream);
     case 3: return launch_pipe<wg::Pipeline<T, 128, 128, 64, 2, 2, 2, false, true>, 128, 128, 64, 2>(p, workgroups, stream);
     case 4: return launch_pipe<wg::Pipeline<T, 128, 128, 64, 2, 2, 2, true, true>, 128, 128, 64, 2>(p, workgroups, stream);
+    case 9: return launch_pipe<wg::Pipeline<T, 256, 256, 64, 2, 2, 2, true>, 256, 256, 64, 2>(p, workgroups, stream);
+    case 10: return launch_pipe<wg::Pipeline<T, 256, 256, 64, 2, 2, 2, false, true>, 256, 256, 64, 2>(p, workgroups, stream);
+    case 11: return launch_pipe<wg::Pipeline<T, 256, 256, 64, 2, 2, 2, true, true>, 256, 256, 64, 2>(p, workgroups, stream);
     default: return hipErrorInvalidValue;
     }
 }

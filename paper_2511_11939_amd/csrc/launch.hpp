@@ -13,7 +13,8 @@ struct PipeConfig {
     int tile_m, tile_n, tile_k, waves, stages;
     const char* name;
 };
-constexpr int kNumPipeConfigs = 9;  // 0, 1: both operands K-contiguous; 2-4: B along n, A along m, both; 5-8: fp32, same four
+// 0, 1: both operands K-contiguous; 2-4: B along n, A along m, both; 5-8: fp32, same four; 9-11: 2-4 with large tiles
+constexpr int kNumPipeConfigs = 12;
 extern const PipeConfig kPipeConfigs[kNumPipeConfigs];
 
 constexpr int kStagedTileM = 128, kStagedTileN = 128, kStagedWaves = 4;

@@ -161,10 +161,11 @@ struct Pipeline {
     using L = lane::TileLayout<BK>;
     static constexpr int ES = Frag<T>::kElemBytes;
     static constexpr int K_PER_STEP = L::kRowBytes / ES;  // elements of K one step consumes (BK counts 2-byte units)
-    // (A 256x256 form of the k-row variants was built twice; beside 256 accumulators it spills
-    // several hundred registers and runs at half the speed of the 128x128 form.)
-    static_assert(!B_KN || (BK == 64 && BN == 128), "n-contiguous B: k-rows of 128 elements");
-    static_assert(!A_MK || (BK == 64 && BM == 128), "m-contiguous A: k-rows of 128 elements");
+    // Every read of a k-row tile is one of four per-lane addresses kept in registers plus a
+    // constant, as with the rows of a K-contiguous operand; addresses worked out per read would
+    // not fit beside the 256 accumulators of the 256x256 tile (several hundred spills).
+    static_assert(!B_KN || (BK == 64 && (BN == 128 || (BN == 256 && ES == 2))), "n-contiguous B: k-rows of 128 or 256 elements");
+    static_assert(!A_MK || (BK == 64 && (BM == 128 || (BM == 256 && ES == 2))), "m-contiguous A: k-rows of 128 or 256 elements");
     static_assert(!(A_MK && B_KN) || BM == BN, "both operands as k-rows: square tile");
     // A K-contiguous B is dealt to the LDS rows in the paired order (lane::paired_tile_row), so
     // that the epilogue can store from the registers; the k-row form keeps the plain order.
@@ -216,8 +217,7 @@ struct Pipeline {
         const persp::Wave wv = wgp.wave();  // every wave of the workgroup runs this code
         constexpr int PARTS = wave::mfma_parts(frag_t{});  // matrix instructions per block and sub-step
         constexpr int NM = MT * NT * PARTS;                // MFMAs per sub-step
-        constexpr int A_READS = A_MK && ES == 2 ? 2 : 1, B_READS = B_KN && ES == 2 ? 2 : 1;  // LDS reads per fragment
-        constexpr int NR = A_READS * MT + B_READS * NT;                // fragment reads per sub-step
+        constexpr int NR = MT + NT;                        // fragments to read per sub-step
         // -- per-lane copy offsets: wave-copy i moves row block (i*NW + wave) of COPY_ROWS rows;
         //    a lane fills one chunk position of one row with the logical chunk the swizzle wants.
         // (row pitches in bytes stay below 2^24 and rows below 2^8 -- the host refuses larger
@@ -288,14 +288,6 @@ struct Pipeline {
             }
         __builtin_amdgcn_sched_barrier(0);
 
-        // 16-bit operands kept as k-rows: fragments come from the transposing LDS read, see
-        // wave::read_k_rows_half; four per-lane address parts serve all reads.
-        uint32_t k_rows_part[4];
-#pragma unroll
-        for (int jl = 0; jl < 4; ++jl) k_rows_part[jl] = wave::k_rows_lane_part<KN_ROW_BYTES>(wv, jl, lane);
-        auto read_k_rows = [&](const char* tile, int row0, int j, int ksub, int h) __attribute__((always_inline)) {
-            return wave::read_k_rows_half<KN_ROW_BYTES>(wv, tile, row0, j, ksub, h, k_rows_part);
-        };
         // fp32 fragment from k-rows: element e of lane (x, g) is the value at k-row 16*ksub + 4g + e,
         // element first + x; nothing to transpose, four 4-byte reads.
         auto gather_k_rows = [&](const char* tile, int first, int ksub) __attribute__((always_inline)) {
@@ -309,7 +301,20 @@ struct Pipeline {
 
         const int wave_m = wave / WAVES_N, wave_n = wave % WAVES_N;
         const int a_row0 = wave_m * WTM, b_row0 = wave_n * WTN;
-        using v4s = wave::v4s;
+        // 16-bit operands kept as k-rows: fragments come from the transposing LDS read, see
+        // wave::read_k_rows_half; four per-lane addresses and constants serve all reads.
+        uint32_t ka_off[4], kb_off[4];
+        if constexpr (ES == 2 && (A_MK || B_KN)) {
+            static_assert(WTM % 64 == 0 && WTN % 64 == 0, "wave tiles start at whole groups of 64 elements");
+#pragma unroll
+            for (int jl = 0; jl < 4; ++jl) {
+                const uint32_t part = wave::k_rows_lane_part<KN_ROW_BYTES>(wv, jl, lane);
+                ka_off[jl] = a_row0 * ES + part;
+                kb_off[jl] = b_slot(0) + b_row0 * ES + part;
+                if constexpr (A_MK) asm volatile("" : "+v"(ka_off[jl]));
+                if constexpr (B_KN) asm volatile("" : "+v"(kb_off[jl]));
+            }
+        }
         static_assert(WTM % 8 == 0 && WTN % 8 == 0 && lane::kBlock % 8 == 0, "row blocks start at multiples of 8 rows");
         // The lane's share of a fragment address, one per operand and sub-step: wave tile's first
         // row, the lane's row and chunk inside a block, and for B the start of the B tiles.  Every
@@ -323,38 +328,35 @@ struct Pipeline {
             asm volatile("" : "+v"(fa_off[ks]), "+v"(fb_off[ks]));  // kept in registers, not re-derived per read
         }
         frag_t fa[2][MT], fb[2][NT];
-        v4s fah[2][MT][2], fbh[2][NT][2];  // operands kept as k-rows: the two halves of every fragment
         // read number r (0 .. NR-1) of sub-step ksub of slot `stage` into buffer `buf`;
         // order: a0, all b, remaining a -- what the first MFMAs of the next group need first
-        auto read_a = [&](int x, int buf, int stage, int ksub) __attribute__((always_inline)) {  // x: fragment * A_READS + half
+        // (the two halves of a fragment from k-rows are read in one place and brought together at
+        // once: kept as two values over the slots between them they end up in registers apart)
+        auto read_halves = [&](const char* st, int j, int ksub, const uint32_t (&part)[4]) __attribute__((always_inline)) {
+            const wave::v4s lo = wave::read_k_rows_half<KN_ROW_BYTES>(wv, st, 0, j, ksub, 0, part);
+            const wave::v4s hi = wave::read_k_rows_half<KN_ROW_BYTES>(wv, st, 0, j, ksub, 1, part);
+            return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        };
+        auto read_a = [&](int x, int buf, int stage, int ksub) __attribute__((always_inline)) {
             const char* st = lds + a_slot(stage);
-            if constexpr (A_MK && ES == 2) fah[buf][x / 2][x % 2] = read_k_rows(st, a_row0, x / 2, ksub, x % 2);
+            if constexpr (A_MK && ES == 2) fa[buf][x] = __builtin_bit_cast(frag_t, read_halves(st, x, ksub, ka_off));
             else if constexpr (A_MK) fa[buf][x] = __builtin_bit_cast(frag_t, gather_k_rows(st, a_row0 + lane::kBlock * x, ksub));
             else fa[buf][x] = lane::load_fragment_at<T>(wv.lane(), st + lane::kBlock * x * L::kRowBytes, fa_off[ksub]);
         };
         auto read_b = [&](int x, int buf, int stage, int ksub) __attribute__((always_inline)) {
             const char* st = lds + b_slot(stage);
-            if constexpr (B_KN && ES == 2) fbh[buf][x / 2][x % 2] = read_k_rows(st, b_row0, x / 2, ksub, x % 2);
+            if constexpr (B_KN && ES == 2) fb[buf][x] = __builtin_bit_cast(frag_t, read_halves(st - b_slot(0), x, ksub, kb_off));
             else if constexpr (B_KN) fb[buf][x] = __builtin_bit_cast(frag_t, gather_k_rows(st, b_row0 + lane::kBlock * x, ksub));
             else fb[buf][x] = lane::load_fragment_at<T>(wv.lane(), st - b_slot(0) + lane::kBlock * x * L::kRowBytes, fb_off[ksub]);
         };
         auto read = [&](int r, int buf, int stage, int ksub) __attribute__((always_inline)) {
-            if (r < A_READS) read_a(r, buf, stage, ksub);
-            else if (r < A_READS + B_READS * NT) read_b(r - A_READS, buf, stage, ksub);
-            else read_a(r - B_READS * NT, buf, stage, ksub);
-        };
-        auto whole = [](v4s lo, v4s hi) __attribute__((always_inline)) {
-            if constexpr (ES == 2) return __builtin_bit_cast(frag_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-            else return frag_t{};
+            if (r == 0) read_a(0, buf, stage, ksub);
+            else if (r <= NT) read_b(r - 1, buf, stage, ksub);
+            else read_a(r - NT, buf, stage, ksub);
         };
         auto mfma = [&](int m, int buf) __attribute__((always_inline)) {
             const int e = m / (MT * NT), blk = m % (MT * NT), i = blk / NT, j = blk % NT;
-            frag_t a, b;
-            if constexpr (A_MK && ES == 2) a = whole(fah[buf][i][0], fah[buf][i][1]);
-            else a = fa[buf][i];
-            if constexpr (B_KN && ES == 2) b = whole(fbh[buf][j][0], fbh[buf][j][1]);
-            else b = fb[buf][j];
-            acc.acc[i][j] = wave::mfma_part(wv, b, a, e, acc.acc[i][j]);
+            acc.acc[i][j] = wave::mfma_part(wv, fb[buf][j], fa[buf][i], e, acc.acc[i][j]);
         };
 
         // -- prologue, second part: wait for step 0, fetch its first fragments
@@ -436,6 +438,61 @@ struct Pipeline {
         // step t's copies: the first TAILN issued after the hand-over of step t-2, the rest in
         // sub-step 0 of step t-1; steps 0 and 1 came whole from the prologue.
         int t = 0;
+        if constexpr (MT * NT == 64 && (A_MK || B_KN)) {
+            // The large tile with k-rows compiles without spills and without moving accumulators
+            // about only as one small loop: a single step per trip, the slot toggled in the address
+            // registers, no branch around a copy (past the end the copies fetch the last step
+            // again into slots that nobody reads).  Measured against 128x128 tiles, which the LDS
+            // reads of their smaller wave tiles bound: 8192 x 4096 x 4096 row-major B 232 -> 191 us,
+            // 4096 x 4096 x 8192 column-major A, row-major B, fp32 C with beta 278 -> 209 us.
+            static_assert(KSUB == 2 && HEADN == 0 && A_BYTES == 32768 && B_BYTES == 32768 && STAGES == 2, "the slot is bit 15 of an LDS address");
+            auto pin_acc = [&]() __attribute__((always_inline)) {
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j) asm volatile("" : "+a"(acc.acc[i][j]));
+            };
+            auto toggle = [&](uint32_t& address) __attribute__((always_inline)) {
+                address ^= 32768u;
+                asm volatile("" : "+v"(address));
+            };
+            pin_acc();
+            for (; t < ksteps; ++t) {
+#pragma unroll
+                for (int m = 0; m < NM; ++m) {
+                    if (m % READ_SPACING == 0 && m / READ_SPACING < NR) read(m / READ_SPACING, 1, 0, 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    mfma(m, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                PRISM_PARANOID_SYNC(wgp);
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    if constexpr (A_MK) toggle(ka_off[x]);
+                    else if (x < KSUB) toggle(fa_off[x]);
+                    if constexpr (B_KN) toggle(kb_off[x]);
+                    else if (x < KSUB) toggle(fb_off[x]);
+                }
+                const int after_next = (t + 2 < ksteps ? t + 2 : ksteps - 1), stage = t & 1;
+                wait_counts<0, 0>();
+                barrier(wgp);
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int m = 0; m < NM; ++m) {
+                    if (m % READ_SPACING == 0 && m / READ_SPACING < NR) read(m / READ_SPACING, 0, 0, 0);
+                    if (m % TAIL_SPACING == 1 && m / TAIL_SPACING < COPIES) copy(m / TAIL_SPACING, after_next, stage);
+                    __builtin_amdgcn_sched_barrier(0);
+                    mfma(m, 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                PRISM_PARANOID_SYNC(wgp);
+            }
+            pin_acc();
+            wait_counts<0, 0>();  // the copies issued past the end
+            __builtin_amdgcn_sched_barrier(0);
+            return;
+        }
         if (ksteps == 1) {
             k_step(no{}, no{}, yes{}, 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
