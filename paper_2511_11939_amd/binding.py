@@ -32,6 +32,7 @@ class Layout(enum.IntEnum):
     COL = 1
 
 
+_ROW = int(Layout.ROW)
 _DTYPE_NAMES = {"bf16": DType.BF16, "f16": DType.F16, "f32": DType.F32}
 _LAYOUT_NAMES = {"row": Layout.ROW, "col": Layout.COL}
 
@@ -229,31 +230,55 @@ def make_desc(ab_dtype="bf16", c_dtype="bf16", layout_a="row", layout_b="col", l
     return d
 
 
+_current_stream = None
+
+
+def _stream(stream) -> int:
+    """The hipStream_t of a torch stream, of a raw value or (None) of torch's current stream.
+
+    Every call asks for the current stream, and torch.cuda.current_stream() builds a Stream object
+    first: 2.8 us of a call that takes 8.  The raw handle is asked for by device index instead."""
+    global _current_stream
+    if stream is not None:
+        return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+    if _current_stream is None:
+        import torch
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is None:
+            _current_stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
+        else:
+            device = torch.cuda.current_device
+            _current_stream = lambda: raw(device())  # noqa: E731
+    return _current_stream()
+
+
 def gemm(A, B, C, *, M, N, K, desc: GemmDesc, lda=None, ldb=None, ldc=None, batch=1,
          strideA=None, strideB=None, strideC=None, stream=None):
     """Enqueue C <- alpha*A*B + bias + beta*C on `stream` (a torch.cuda.Stream, a raw
     hipStream_t value or None for torch's current stream).  A, B, C: device tensors or
     raw device pointers, laid out as `desc` says.  Raises PrismError on a bad status."""
     if lda is None:
-        lda = K if desc.layout_a == Layout.ROW else M
+        lda = (K if desc.layout_a == _ROW else M) or 1
     if ldb is None:
-        ldb = N if desc.layout_b == Layout.ROW else K
+        ldb = (N if desc.layout_b == _ROW else K) or 1
     if ldc is None:
-        ldc = N if desc.layout_c == Layout.ROW else M
-    if stream is None:
-        import torch
-        stream = torch.cuda.current_stream().cuda_stream
-    elif hasattr(stream, "cuda_stream"):
-        stream = stream.cuda_stream
-    if batch == 1 and strideA is None and strideB is None and strideC is None:
-        s = prism_gemm(desc, M, N, K, A, max(lda, 1), B, max(ldb, 1), C, max(ldc, 1), stream)
+        ldc = (N if desc.layout_c == _ROW else M) or 1
+    lib = _lib or load_library()
+    single = batch == 1 and strideA is None and strideB is None and strideC is None
+    # (the pointers of the usual case, three tensors, without the questions that _p asks)
+    try:
+        A, B, C = A.data_ptr(), B.data_ptr(), C.data_ptr()
+    except AttributeError:
+        A, B, C = _p(A), _p(B), _p(C)
+    if single:
+        s = lib.prism_gemm(_descp(desc), M, N, K, A, max(lda, 1), B, max(ldb, 1), C, max(ldc, 1), _stream(stream))
     else:
         strideA = M * K if strideA is None else strideA
         strideB = K * N if strideB is None else strideB
         strideC = M * N if strideC is None else strideC
-        s = prism_gemm_batched(desc, M, N, K, A, max(lda, 1), strideA, B, max(ldb, 1), strideB,
-                               C, max(ldc, 1), strideC, batch, stream)
-    if s != Status.OK:
+        s = lib.prism_gemm_batched(_descp(desc), M, N, K, A, max(lda, 1), strideA, B, max(ldb, 1), strideB,
+                                   C, max(ldc, 1), strideC, batch, _stream(stream))
+    if s != 0:
         raise PrismError(s, "prism_gemm")
 
 
@@ -281,12 +306,8 @@ def scan_u32(inp, out, n, workspace, *, stream=None):
     """Enqueue the inclusive uint32 prefix sum of `inp` into `out` (may be the same tensor) on
     `stream` (torch stream, raw hipStream_t or None for torch's current stream).  `workspace`:
     a device tensor of at least prism_scan_workspace_size(n) bytes.  Raises on a bad status."""
-    if stream is None:
-        import torch
-        stream = torch.cuda.current_stream().cuda_stream
-    elif hasattr(stream, "cuda_stream"):
-        stream = stream.cuda_stream
     nbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    s = prism_scan_u32(inp, out, n, workspace, nbytes, stream)
-    if s != Status.OK:
+    lib = _lib or load_library()
+    s = lib.prism_scan_u32(_p(inp), _p(out), n, _p(workspace), nbytes, _stream(stream))
+    if s != 0:
         raise PrismError(s, "prism_scan_u32")
