@@ -87,7 +87,9 @@ typedef struct prism_gemm_plan {
     int32_t kernel;          /* 0 = nothing to launch, 1 = staged (any layout/alignment),
                                 2 = direct-to-LDS pipeline (aligned operands),
                                 3 = the same pipeline, persistent: used for more tiles
-                                    than compute units with short K loops              */
+                                    than compute units with short K loops,
+                                4 = few rows (C, or C^T when swapped, has at most 64):
+                                    whole sums per workgroup, no tile loop, no split   */
     int32_t tile_m, tile_n, tile_k; /* workgroup tile                                */
     int32_t waves;           /* wavefronts per workgroup                              */
     int32_t split_k;         /* K slices actually used (>= 1)                         */
@@ -203,7 +205,8 @@ PRISM_API prism_status_t prism_mfma_probe(int32_t ab_dtype, const void* operands
  *       2 K loop done, 3 results stored and acknowledged.
  * Differences of cycles over differences of ticks give the clock the GPU sustained in a
  * phase; workgroup g runs on die g % 8.  Only problems that prism_gemm_plan sends to the
- * direct-to-LDS pipeline (plan.kernel == 2) can be stamped, others are PRISM_ERR_UNSUPPORTED.
+ * direct-to-LDS pipeline or to the kernel for few rows (plan.kernel == 2 or 4) can be stamped, others
+ * are PRISM_ERR_UNSUPPORTED.
  * stamps: device, 8-byte aligned, plan.workgroups * PRISM_STAMP_BYTES_PER_WORKGROUP bytes or
  * more (else PRISM_ERR_WORKSPACE).  Everything else as prism_gemm_batched.
  */

@@ -11,7 +11,7 @@ LIB_PATH = os.path.join(_HERE, "libprism_gemm.so")
 # the same library with a workgroup barrier after every LDS phase of the main loops (race check:
 # its results must equal the normal build's bit for bit)
 PARANOID_LIB_PATH = os.path.join(_HERE, "libprism_gemm_paranoid.so")
-_UNITS = ["kernels.hip", "host_api.hip", "scan.hip", "probe.hip"]
+_UNITS = ["kernels.hip", "skinny.hip", "host_api.hip", "scan.hip", "probe.hip"]
 _FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
     # keep the compiler from forming packed fp32 vector ops out of scalar float code

@@ -18,6 +18,8 @@ using prism::GemmParams;
 
 constexpr int kComputeUnits = 256;
 constexpr int kPersistentMaxSteps = 16;  // longest K loop (in K steps) the persistent kernel is chosen for
+constexpr int kSkinnyRows = 64;          // rows of C up to which the kernel for few rows is chosen
+constexpr int64_t kSkinnyBytes = 3 << 19;  // operand bytes per workgroup beyond which tiles and a K split win
 constexpr int kMaxSplit = 64;
 constexpr int kVeryLongK = 512;              // K steps from which few 256x256 tiles with many slices beat small tiles
 constexpr int kMinSliceStepsStaged = 8;      // shortest K loop (in K steps) a slice of the staged kernel gets
@@ -53,7 +55,7 @@ bool overlaps(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes)
 
 // Hooks for tests and experiments, read from the environment once (at the first call that
 // needs them, or again on prism_reread_environment) and kept:
-//   PRISM_GEMM_CONFIG=<index>  pins the pipeline's tile configuration (0: 256x256, 1: 128x128)
+//   PRISM_GEMM_CONFIG=<index>  pins the pipeline's tile configuration (0: 256x256, 1: 128x128), few rows or not
 //   PRISM_PERSISTENT=0|1       never / whenever possible use the persistent kernel
 //   PRISM_LOG=1                one line per launch on stderr: problem, kernel, tile, split
 struct Hooks {
@@ -184,6 +186,33 @@ prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, in
     const bool b_along_n = p.b_sn == 1 && p.b_sk != 1 && aligned(p.B, 16) && p.b_sk % epc == 0 && p.N % epc == 0 &&
                            (p.batch == 1 || p.batch_b % epc == 0);
     const bool pipe_ok = (p.a_vec || a_along_m) && (p.b_vec || b_along_n) && K % step_k == 0 && pitch_ok;
+    // ---- few rows: no tile loop and no split, see skinny.hip.  Both operands K-contiguous, K at
+    // least a chunk.  Not for more than 32 rows where 128x128 tiles give half of the compute units a
+    // workgroup, because every 16 or 32 columns read all rows of A again (64 x 16384 x 4096: 39.2 us
+    // with tiles, 41.3 without; 128 problems of 64 x 512 x 512: 24.4 and 38.6), and not where few
+    // workgroups would each have a very long way to go (64 x 512 x 16384, 2.6 MB each: 19.6 us with
+    // tiles and a K split, 27.7 without; 64 x 4096 x 4096, 0.65 MB each: 16.5 and 11.6).
+    const int64_t skinny_m = p.M <= 16 ? 16 : p.M <= 32 ? 32 : 64, skinny_n = ceil_div(p.N, 32) * batch >= kComputeUnits ? 32 : 16;
+    const bool many_tiles = p.M > 32 && pipe_ok && ceil_div(p.N, prism::kStagedTileN) * batch >= kComputeUnits / 2;
+    const bool long_way = ceil_div(p.N, skinny_n) * batch <= kComputeUnits && (skinny_m + skinny_n) * K * ab_esize > kSkinnyBytes && pipe_ok;
+    if (p.M <= kSkinnyRows && a_kfast && b_kfast && K >= epc && pitch_ok && d->split_k <= 1 && hk.pipe_config < 0 && hk.persistent != 1 &&
+        !many_tiles && !long_way) {
+        plan.kernel = 4;
+        plan.tile_m = static_cast<int32_t>(skinny_m);
+        plan.tile_n = static_cast<int32_t>(skinny_n);  // two blocks of columns where that still gives every compute unit a workgroup
+        plan.tile_k = static_cast<int32_t>(step_k);
+        plan.tiles_m = 1;
+        plan.tiles_n = ceil_div(p.N, plan.tile_n);
+        plan.workgroups = plan.tiles_n * batch;
+        // as many waves as have K steps of their own, sixteen only where workgroups are few
+        plan.waves = ksteps >= 32 && plan.workgroups <= kComputeUnits / 2 ? 16 : ksteps >= 8 ? 8 : 4;
+        if (plan.workgroups > kIntMax / 64) return PRISM_ERR_INVALID_ARG;
+        p.split_k = 1;
+        p.k_slice = p.K;
+        p.tiles_m = 1;
+        p.tiles_n = static_cast<int>(plan.tiles_n);
+        return PRISM_OK;
+    }
     int tile_m = prism::kStagedTileM, tile_n = prism::kStagedTileN, waves = prism::kStagedWaves;
     plan.kernel = 1;
     if (pipe_ok) {
@@ -291,12 +320,14 @@ prism_status_t run(const Problem& pr, hipStream_t stream)
         e = prism::launch_pipelined(pr.pipe_config, pr.ab_dtype, p, static_cast<int>(pr.plan.workgroups), stream);
     else if (pr.plan.kernel == 1)
         e = prism::launch_staged(pr.ab_dtype, p, static_cast<int>(pr.plan.workgroups), stream);
+    else if (pr.plan.kernel == 4)
+        e = prism::launch_skinny(pr.ab_dtype, pr.plan.tile_m, pr.plan.tile_n, pr.plan.waves, p, static_cast<int>(pr.plan.workgroups), stream);
     if (e != hipSuccess) return PRISM_ERR_LAUNCH;
     if (hooks().log) {
-        static const char* const names[] = {"none", "gemm_staged", "gemm_pipelined", "gemm_persistent"};
+        static const char* const names[] = {"none", "gemm_staged", "gemm_pipelined", "gemm_persistent", "gemm_skinny"};
         std::fprintf(stderr, "prism_gemm: M=%d N=%d K=%d batch=%d%s kernel=%s tile=%dx%dx%d waves=%d split_k=%d workgroups=%lld\n",
                      p.M, p.N, p.K, p.batch, pr.plan.swapped ? " (run as C^T = B^T A^T)" : "",
-                     names[pr.plan.kernel >= 0 && pr.plan.kernel <= 3 ? pr.plan.kernel : 0], pr.plan.tile_m, pr.plan.tile_n,
+                     names[pr.plan.kernel >= 0 && pr.plan.kernel <= 4 ? pr.plan.kernel : 0], pr.plan.tile_m, pr.plan.tile_n,
                      pr.plan.tile_k, pr.plan.waves, pr.plan.split_k, static_cast<long long>(pr.plan.workgroups));
     }
     if (p.split_k != 1) {  // K == 0 (split_k == 0) or a real split: the reduction writes C
@@ -331,7 +362,7 @@ prism_status_t prism_gemm_batched_stamped(const prism_gemm_desc_t* d, int64_t M,
     const prism_status_t s =
         make_problem(d, M, N, K, A, lda, strideA, B, ldb, strideB, C, ldc, strideC, batch, true, &pr);
     if (s != PRISM_OK) return s;
-    if (pr.plan.kernel != 2) return PRISM_ERR_UNSUPPORTED;  // only the pipelined kernel leaves stamps
+    if (pr.plan.kernel != 2 && pr.plan.kernel != 4) return PRISM_ERR_UNSUPPORTED;  // the others leave no stamps
     if (!stamps || reinterpret_cast<uintptr_t>(stamps) % 8 != 0) return PRISM_ERR_INVALID_ARG;
     if (stamp_bytes < static_cast<size_t>(pr.plan.workgroups) * PRISM_STAMP_BYTES_PER_WORKGROUP) return PRISM_ERR_WORKSPACE;
     static_assert(PRISM_STAMP_BYTES_PER_WORKGROUP == prism::kStampWords * sizeof(uint64_t), "stamp layout");

@@ -26,6 +26,9 @@ hipError_t launch_staged(int ab_dtype, const GemmParams& p, int workgroups, hipS
 // 256x256x64 tile, `workgroups` persistent workgroups walking `total` (tile, unit) pairs;
 // every unit must span at least two K steps of 64.
 hipError_t launch_persistent(int ab_dtype, const GemmParams& p, int total, int workgroups, hipStream_t stream);
+// Few rows: `workgroups` = tiles_n * batch workgroups of `waves` (4, 8 or 16) waves; tile_m (16, 32
+// or 64) covers p.M, tile_n is 16 or 32.
+hipError_t launch_skinny(int ab_dtype, int tile_m, int tile_n, int waves, const GemmParams& p, int workgroups, hipStream_t stream);
 // Sums the split_k partial slabs in slice order and applies the epilogue; with
 // p.split_k == 0 it writes C <- bias + beta*C (the K == 0 case).
 hipError_t launch_reduce(const GemmParams& p, hipStream_t stream);
