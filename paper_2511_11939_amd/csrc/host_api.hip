@@ -19,6 +19,7 @@ using prism::GemmParams;
 constexpr int kComputeUnits = 256;
 constexpr int kPersistentMaxSteps = 16;  // longest K loop (in K steps) the persistent kernel is chosen for
 constexpr int kSkinnyRows = 64;          // rows of C up to which the kernel for few rows is chosen
+constexpr int64_t kSkinnyMaxWorkgroups = 1 << 21;  // of 1024 threads: what one launch takes; tiles of 128 columns beyond
 constexpr int64_t kSkinnyBytes = 3 << 19;  // operand bytes per workgroup beyond which tiles and a K split win
 constexpr int kMaxSplit = 64;
 constexpr int kVeryLongK = 512;              // K steps from which few 256x256 tiles with many slices beat small tiles
@@ -91,7 +92,7 @@ Hooks hooks()
 prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, int64_t K,
                             const void* A, int64_t lda, int64_t strideA, const void* B, int64_t ldb,
                             int64_t strideB, const void* C, int64_t ldc, int64_t strideC, int64_t batch,
-                            bool need_pointers, Problem* out)
+                            bool need_pointers, Problem* out, bool allow_few_rows = true)
 {
     if (!d || !out) return PRISM_ERR_INVALID_ARG;
     if (!valid_dtype_ab(d->ab_dtype) || !valid_dtype_c(d->c_dtype) || !valid_layout(d->layout_a) ||
@@ -195,8 +196,9 @@ prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, in
     const int64_t skinny_m = p.M <= 16 ? 16 : p.M <= 32 ? 32 : 64, skinny_n = ceil_div(p.N, 32) * batch >= kComputeUnits ? 32 : 16;
     const bool many_tiles = p.M > 32 && pipe_ok && ceil_div(p.N, prism::kStagedTileN) * batch >= kComputeUnits / 2;
     const bool long_way = ceil_div(p.N, skinny_n) * batch <= kComputeUnits && (skinny_m + skinny_n) * K * ab_esize > kSkinnyBytes && pipe_ok;
-    if (p.M <= kSkinnyRows && a_kfast && b_kfast && K >= epc && pitch_ok && d->split_k <= 1 && hk.pipe_config < 0 && hk.persistent != 1 &&
-        !many_tiles && !long_way) {
+    const bool grid_fits = ceil_div(p.N, skinny_n) * batch <= kSkinnyMaxWorkgroups;
+    if (allow_few_rows && p.M <= kSkinnyRows && a_kfast && b_kfast && K >= epc && pitch_ok && d->split_k <= 1 && hk.pipe_config < 0 &&
+        hk.persistent != 1 && grid_fits && !many_tiles && !long_way) {
         plan.kernel = 4;
         plan.tile_m = static_cast<int32_t>(skinny_m);
         plan.tile_n = static_cast<int32_t>(skinny_n);  // two blocks of columns where that still gives every compute unit a workgroup
@@ -206,7 +208,6 @@ prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, in
         plan.workgroups = plan.tiles_n * batch;
         // as many waves as have K steps of their own, sixteen only where workgroups are few
         plan.waves = ksteps >= 32 && plan.workgroups <= kComputeUnits / 2 ? 16 : ksteps >= 8 ? 8 : 4;
-        if (plan.workgroups > kIntMax / 64) return PRISM_ERR_INVALID_ARG;
         p.split_k = 1;
         p.k_slice = p.K;
         p.tiles_m = 1;
@@ -362,6 +363,9 @@ prism_status_t prism_gemm_batched_stamped(const prism_gemm_desc_t* d, int64_t M,
     const prism_status_t s =
         make_problem(d, M, N, K, A, lda, strideA, B, ldb, strideB, C, ldc, strideC, batch, true, &pr);
     if (s != PRISM_OK) return s;
+    // (stamps for fewer workgroups than the kernel for few rows has may be enough for its tiles)
+    if (pr.plan.kernel == 4 && stamps && stamp_bytes < static_cast<size_t>(pr.plan.workgroups) * PRISM_STAMP_BYTES_PER_WORKGROUP)
+        make_problem(d, M, N, K, A, lda, strideA, B, ldb, strideB, C, ldc, strideC, batch, true, &pr, false);
     if (pr.plan.kernel != 2 && pr.plan.kernel != 4) return PRISM_ERR_UNSUPPORTED;  // the others leave no stamps
     if (!stamps || reinterpret_cast<uintptr_t>(stamps) % 8 != 0) return PRISM_ERR_INVALID_ARG;
     if (stamp_bytes < static_cast<size_t>(pr.plan.workgroups) * PRISM_STAMP_BYTES_PER_WORKGROUP) return PRISM_ERR_WORKSPACE;
