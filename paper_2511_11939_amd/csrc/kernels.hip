@@ -331,7 +331,8 @@ __global__ __launch_bounds__(256, 2) void gemm_staged(const GemmParams p)
 // asked for before the first is added (4 slices of 16 x 4096: the call 16.4 -> 15.2 us; 19 of
 // 640 x 192: 51.8 -> 49.0).  More than that are bound by memory, where a wave that asks for
 // several slices, megabytes apart, at a time is slower (16 slices of 1024 x 1024: 84.6 us one by
-// one, 85.7 with four, 86.4 with eight ahead).
+// one, 85.7 with four, 86.4 with eight ahead) and where each is read once: as a stream the same call
+// takes 81.9 us.
 __global__ __launch_bounds__(256) void splitk_reduce(const GemmParams p)
 {
     constexpr int kAhead = 4;
@@ -358,7 +359,7 @@ __global__ __launch_bounds__(256) void splitk_reduce(const GemmParams p)
         f32x4 sum = {0.f, 0.f, 0.f, 0.f};
         const char* src = reinterpret_cast<const char*>(p.partial + static_cast<int64_t>(b) * p.split_k * slab + static_cast<int64_t>(m) * p.N + n0);
         if (left >= 4 && !ahead) {
-            for (int s = 0; s < p.split_k; ++s, src += 4 * slab) sum += grid::load4<DT_F32>(src);
+            for (int s = 0; s < p.split_k; ++s, src += 4 * slab) sum += __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(src));
         } else if (left >= 4) {
             int s = 0;
             for (; s + kAhead <= p.split_k; s += kAhead, src += 4 * kAhead * slab) {
