@@ -732,11 +732,13 @@ struct PersistentPipe {
 // So two K steps are in flight in registers beside the two in LDS (a load issued in step t is
 // written to LDS in step t + 2 and used in step t + 3), and a step has one barrier.  Measured:
 // 1999 x 2001 x 1003 bf16, odd pitches, 24.2 us (131.8 us with element loads for every unaligned
-// chunk and one LDS slot); 960 x 3072 x 3733, row-major B, 53 us (329).
+// chunk and one LDS slot); 960 x 3072 x 3733, row-major B, 53 us (329); 4 x 978 x 10368, column-major A,
+// row-major B, 118 us (364 without anything in flight, as is still done where a step is the only one).
 //
 // Only the last K step can hold k beyond the matrix or read past an operand's last element.  It
 // is computed first and takes the careful fetch: chunks are loaded from where they lie wholly inside their row and
-// moved into place in registers, zeros behind.  All other steps are loads at a uniform base plus
+// moved into place in registers, zeros behind (from a k-row shorter than a chunk the chunk is the 16
+// bytes that end with it: the rows before it lie there).  All other steps are loads at a uniform base plus
 // fixed per-lane offsets: rows beyond the matrix re-read its last row, and a chunk that
 // straddles the end of a k-row brings elements of the next one, which only feed results that
 // are never stored.
@@ -809,7 +811,14 @@ struct StagedOperand {
         }
     }
     // can a K step inside the matrix be fetched by fixed 32-bit offsets?
-    __device__ __forceinline__ bool regular() const { return !narrow && pitch < (int64_t{1} << 31) / (K_ROWS ? BK : EXT) - 1024; }
+    __device__ __forceinline__ bool regular() const { return pitch < (int64_t{1} << 31) / (K_ROWS ? BK : EXT) - 1024; }
+    // With `k_left` >= 1 rows of the matrix after them: do the fixed 16-byte loads of a step's k-rows stay
+    // inside the operand?  A k-row of a chunk or more reaches at most into the next one; a shorter
+    // one's only chunk may reach over several.
+    __device__ __forceinline__ bool stays_inside(int k_left) const
+    {
+        return !K_ROWS || !narrow || k_left * pitch + rows * ES >= lane::kChunkBytes;
+    }
 
     __device__ __forceinline__ void fetch(u32x4 (&regs)[CHUNKS], int k0)
     {
@@ -935,13 +944,17 @@ struct Staged {
         a.init(a_tile, a_sm, a_sk, a_rows, a_extent, tid);
         b.init(b_tile, b_sn, b_sk, b_rows, b_extent, tid);
         const int steps = (k_end - k_begin + BK - 1) / BK;
-        const bool regular = a.regular() && b.regular() && steps > 1;
+        // Steps fetched by fixed offsets: all but the last, or but the last two where those loads would
+        // run past the end of an operand with very short k-rows.
+        const int k_left = K - (k_begin + (steps - 1) * BK);
+        const int fixed = a.stays_inside(k_left) && b.stays_inside(k_left) ? steps - 1 : steps - 2;
+        const bool regular = a.regular() && b.regular() && fixed > 0;
 
         u32x4 ra[2][A::CHUNKS], rb[2][B::CHUNKS];  // two K steps on their way
         // Step t (past the end: the last whole one again, never used, so that the loop has no
         // branch around a load and waits for exactly the loads it needs)
         auto fetch = [&](int t, int set) __attribute__((always_inline)) {
-            const int k0 = k_begin + (t < steps - 2 ? t : steps - 2) * BK;
+            const int k0 = k_begin + (t < fixed - 1 ? t : fixed - 1) * BK;
             a.fetch(ra[set], k0);
             b.fetch(rb[set], k0);
         };
@@ -986,6 +999,15 @@ struct Staged {
             }
             return;
         }
+        if (fixed < steps - 1) {
+            a.template fetch_careful<false>(ca, k_begin + fixed * BK, k_end);
+            b.template fetch_careful<false>(cb, k_begin + fixed * BK, k_end);
+            a.commit(ca, lds + a_slot(1));
+            b.commit(cb, lds + b_slot(1));
+            hand_over();
+            compute(1);
+            hand_over();
+        }
         // The last step goes first, through slot 1, while the first two travel.
         fetch(0, 0);
         fetch(1, 1);
@@ -1007,10 +1029,10 @@ struct Staged {
             fetch(t + 3, slot ^ 1);
             __builtin_amdgcn_sched_barrier(0);  // the loads set out before the matrix instructions
             PRISM_PARANOID_SYNC(wgp);
-            if (slot == 0 || t < steps - 1) compute(slot);
+            if (slot == 0 || t < fixed) compute(slot);
             hand_over();
         };
-        for (int t = 0; t < steps - 1; t += 2) {
+        for (int t = 0; t < fixed; t += 2) {
             step(t, 0);
             step(t + 1, 1);
         }
