@@ -3,6 +3,7 @@
 // here; everything numeric runs in the device kernels.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -25,6 +26,7 @@ constexpr int kMaxSplit = 64;
 constexpr int kVeryLongK = 512;              // K steps from which few 256x256 tiles with many slices beat small tiles
 constexpr int kMinSliceStepsStaged = 8;      // shortest K loop (in K steps) a slice of the staged kernel gets
 constexpr int64_t kIntMax = 2147483647;
+constexpr int64_t kMaxTiles = kIntMax / 64;  // output tiles of all problems of a call
 
 struct Problem {
     GemmParams p;
@@ -86,6 +88,65 @@ Hooks hooks()
     std::lock_guard<std::mutex> lock(g_hooks_mutex);
     if (!g_hooks_loaded) load_hooks_locked();
     return g_hooks;
+}
+
+// ---- K split: the library's own choice of slices for `units` output tiles (of all problems).
+// A split costs a round trip of fp32 partial sums and a second kernel: it pays only for
+// a long K loop, and every slice must keep a K loop of its own.  Small tiles run two
+// workgroups per compute unit, so they are split until there are about twice as many
+// workgroups as compute units (measured: 512x512x16384 23 us with 16 slices, 28 with
+// 8 or 32).  short_steps: 16-bit operands on the pipeline (a K step of fp32 operands holds four
+// times the matrix instructions).
+int64_t slices_wanted(int64_t units, int64_t ksteps, bool small_tiles, bool short_steps)
+{
+    const int64_t slots = small_tiles ? 2 * kComputeUnits : kComputeUnits;
+    const int64_t min_slice = !short_steps ? kMinSliceStepsStaged : (small_tiles ? 16 : 32);
+    const int64_t min_k = !short_steps ? 4 * kMinSliceStepsStaged : 64;
+    if (units * 2 > slots || ksteps < min_k) return 1;
+    int64_t want = slots / units;
+    if (want > ksteps / min_slice) want = ksteps / min_slice;
+    if (small_tiles && want > 32) want = 32;
+    if (want > kMaxSplit) want = kMaxSplit;
+    return want < 1 ? 1 : want;
+}
+struct Slices {
+    int64_t count, steps;  // slices, none of them empty, and K steps of each but the last
+};
+Slices slices_of(int64_t want, int64_t ksteps)
+{
+    const int64_t steps = ceil_div(ksteps, want < ksteps ? want : ksteps);
+    return Slices{ceil_div(ksteps, steps), steps};
+}
+
+// ---- 256x256 or 128x128 tiles where an operand is not contiguous along K: whichever the measured
+// times of a K step and of a round of workgroups predict to be faster.  (Microseconds.  Large tiles,
+// one workgroup per compute unit: 1.07 per K step, 15.6 per round for the first loads and the
+// epilogue, 5.1 of them hidden in the first; small ones: 1.05 per K step with two workgroups per
+// compute unit, 0.42 where each has one to itself, and 5 per round; the reduction by the megabyte of
+// partial sums.)  The rounds of small tiles with loops of fewer than twelve steps run into each
+// other, and large ones must then be 15 % faster, otherwise 5 %; from kVeryLongK steps on small
+// tiles take a tenth longer than predicted.  Measured over 3400 products of 17 to 4096 rows and columns and 1 to 1024
+// K steps in 1 to 64 problems: 9 are more than 3 % slower than with small tiles (at most 17 %), and
+// 21 more than 5 % slower than with the better choice.  Taking large tiles for 128 of them or for any very
+// long K was up to three times slower: 256 x 256 x 65536 has 32 slices of one large tile, 128 of small ones.
+bool large_k_row_tiles(int64_t M, int64_t N, int64_t batch, int64_t ksteps, int64_t requested_split)
+{
+    // (more small tiles than a launch can take: the large ones may still do)
+    if (ceil_div(M, 128) * ceil_div(N, 128) > kMaxTiles / batch) return true;
+    const int64_t large = ceil_div(M, 256) * ceil_div(N, 256) * batch, small = ceil_div(M, 128) * ceil_div(N, 128) * batch;
+    const Slices ls = slices_of(requested_split ? requested_split : slices_wanted(large, ksteps, false, true), ksteps);
+    const Slices ss = slices_of(requested_split ? requested_split : slices_wanted(small, ksteps, true, true), ksteps);
+    const double slab_mb = 4e-6 * static_cast<double>(M) * static_cast<double>(N) * static_cast<double>(batch);
+    const double round_l = 1.07 * static_cast<double>(ls.steps) + 15.6;
+    double t_large = static_cast<double>(ceil_div(large * ls.count, kComputeUnits)) * round_l - 5.1;
+    if (ls.count > 1) t_large += 0.83 * slab_mb * static_cast<double>(ls.count);
+    const bool alone = small * ss.count <= kComputeUnits;
+    const double round_s = (alone ? 0.42 : 1.05) * static_cast<double>(ss.steps) + 5.0;
+    const double pairs = static_cast<double>(small * ss.count) / (2 * kComputeUnits);
+    const double rounds_s = alone || pairs <= 1.0 ? 1.0 : ksteps < 12 ? pairs : std::ceil(pairs);
+    double t_small = rounds_s * round_s - 0.7;
+    if (ss.count > 1) t_small += 4.0 + 0.44 * slab_mb * static_cast<double>(ss.count);
+    return t_large < (ksteps >= kVeryLongK ? 1.05 : ksteps >= 12 ? 0.95 : 0.85) * t_small;
 }
 
 // Validates everything, normalises to a row-major C and chooses the launch.
@@ -226,12 +287,12 @@ prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, in
             // per compute unit.  Measured: 128x128 tiles win on square problems up to 2560^3
             // (2048^3: 26 against 40 us) and on 1024x1024x8192 (30 against 38 us), 256x256 tiles
             // from 3072^3 on and on 1024x1024x32768.
+            // (operands that are not contiguous along K: see large_k_row_tiles)
             const int64_t big = ceil_div(p.M, 256) * ceil_div(p.N, 256) * batch;
-            cfg = (big >= kComputeUnits / 2 || ksteps >= kVeryLongK) ? 0 : 1;
+            if (p.a_vec && p.b_vec) cfg = (big >= kComputeUnits / 2 || ksteps >= kVeryLongK) ? 0 : 1;
+            else cfg = large_k_row_tiles(p.M, p.N, batch, ksteps, d->split_k) ? 0 : 1;
         }
-        // an operand that is not K-contiguous is kept as k-rows in LDS, with either tile (the line
-        // is the same: 6656 x 1792 x 640 with 182 large tiles 22.0 -> 19.9 us, 704 x 2368 x 3456 with
-        // 30 stays on small tiles)
+        // an operand that is not K-contiguous is kept as k-rows in LDS, with either tile
         if (!p.a_vec || !p.b_vec) cfg = (cfg == 0 ? 9 : 2) + (!p.a_vec ? (!p.b_vec ? 2 : 1) : 0);
         // fp32 operands: 128x128 tiles in all four layout pairs
         if (ab_esize == 4) cfg = 5 + (p.b_vec ? 0 : 1) + (p.a_vec ? 0 : 2);
@@ -241,41 +302,20 @@ prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, in
         waves = prism::kPipeConfigs[cfg].waves;
     }
     const int64_t tiles_m = ceil_div(p.M, tile_m), tiles_n = ceil_div(p.N, tile_n);
-    if (tiles_m * tiles_n > kIntMax / 64 || tiles_m * tiles_n * batch > kIntMax / 64) return PRISM_ERR_INVALID_ARG;
+    if (tiles_m * tiles_n > kMaxTiles || tiles_m * tiles_n * batch > kMaxTiles) return PRISM_ERR_INVALID_ARG;
 
     // ---- K split: explicit request, or enough slices to give every compute unit a workgroup
-    int64_t want = d->split_k;
     const int64_t units = tiles_m * tiles_n * batch;
     const size_t slab_bytes = static_cast<size_t>(batch) * p.M * p.N * sizeof(float);
-    if (want == 0) {
-        want = 1;
-        // A split costs a round trip of fp32 partial sums and a second kernel: it pays only for
-        // a long K loop, and every slice must keep a K loop of its own.  Small tiles run two
-        // workgroups per compute unit, so they are split until there are about twice as many
-        // workgroups as compute units (measured: 512x512x16384 23 us with 16 slices, 28 with
-        // 8 or 32).
-        const bool small_tiles = tile_m != 256;
-        const int64_t slots = small_tiles ? 2 * kComputeUnits : kComputeUnits;
-        // (a K step of fp32 operands holds four times the matrix instructions of a 16-bit one)
-        const bool short_steps = plan.kernel == 2 && ab_esize == 2;
-        const int64_t min_slice = !short_steps ? kMinSliceStepsStaged : (small_tiles ? 16 : 32);
-        const int64_t min_k = !short_steps ? 4 * kMinSliceStepsStaged : 64;
-        if (units * 2 <= slots && ksteps >= min_k) {
-            want = slots / units;
-            if (want > ksteps / min_slice) want = ksteps / min_slice;
-            if (small_tiles && want > 32) want = 32;
-            if (want > kMaxSplit) want = kMaxSplit;
-            if (want < 1) want = 1;
-        }
-    }
-    if (want > ksteps) want = ksteps;
-    int64_t slice_steps = ceil_div(ksteps, want);
-    int64_t split = ceil_div(ksteps, slice_steps);  // no empty slices
-    size_t ws_need = split > 1 ? slab_bytes * static_cast<size_t>(split) : 0;
-    if (split > 1 && need_pointers && (!d->workspace || d->workspace_bytes < ws_need)) {
+    const int64_t want = d->split_k ? d->split_k : slices_wanted(units, ksteps, tile_m != 256, plan.kernel == 2 && ab_esize == 2);
+    Slices slices = slices_of(want, ksteps);
+    size_t ws_need = slices.count > 1 ? slab_bytes * static_cast<size_t>(slices.count) : 0;
+    if (slices.count > 1 && need_pointers && (!d->workspace || d->workspace_bytes < ws_need)) {
         if (d->split_k > 1) return PRISM_ERR_WORKSPACE;
-        split = 1; slice_steps = ksteps; ws_need = 0;  // library's own choice: fall back quietly
+        slices = Slices{1, ksteps};  // library's own choice: fall back quietly
+        ws_need = 0;
     }
+    const int64_t split = slices.count, slice_steps = slices.steps;
     p.split_k = static_cast<int>(split);
     p.k_slice = static_cast<int>(slice_steps * step_k);
     p.partial = split > 1 ? static_cast<float*>(d->workspace) : nullptr;
