@@ -142,8 +142,10 @@ PRISM_API prism_status_t prism_gemm_batched(const prism_gemm_desc_t* d, int64_t 
 /*
  * Bytes of device workspace the descriptor's split_k setting needs for this
  * shape: forced n > 1 gives n*batch*M*N*4, split_k == 1 gives 0, and
- * split_k == 0 gives what the library's own choice would use (it falls back to
- * no split when the caller passes a smaller workspace).  Host arithmetic only.
+ * split_k == 0 gives what the library's own choice uses on tiles with packed,
+ * aligned operands (a call that finds less than it would use takes as many
+ * slices as the workspace holds; one that needs none, as plan.workspace_bytes
+ * says, ignores it).  Host arithmetic only.
  */
 PRISM_API prism_status_t prism_gemm_workspace_size(const prism_gemm_desc_t* d, int64_t M, int64_t N,
                                          int64_t K, int64_t batch, size_t* bytes_out);
