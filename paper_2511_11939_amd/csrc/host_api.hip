@@ -21,7 +21,6 @@ constexpr int kComputeUnits = 256;
 constexpr int kPersistentMaxSteps = 16;  // longest K loop (in K steps) the persistent kernel is chosen for
 constexpr int kSkinnyRows = 64;          // rows of C up to which the kernel for few rows is chosen
 constexpr int64_t kSkinnyMaxWorkgroups = 1 << 21;  // of 1024 threads: what one launch takes; tiles of 128 columns beyond
-constexpr int64_t kSkinnyBytes = 3 << 19;  // operand bytes per workgroup beyond which tiles and a K split win
 constexpr int kMaxSplit = 64;
 constexpr int kVeryLongK = 512;              // K steps from which few 256x256 tiles with many slices beat small tiles
 constexpr int kMinSliceStepsStaged = 8;      // shortest K loop (in K steps) a slice of the staged kernel gets
@@ -149,6 +148,55 @@ bool large_k_row_tiles(int64_t M, int64_t N, int64_t batch, int64_t ksteps, int6
     return t_large < (ksteps >= kVeryLongK ? 1.05 : ksteps >= 12 ? 0.95 : 0.85) * t_small;
 }
 
+// ---- few rows: the kernel without tiles, or tiles with a split?  Both are predicted from times measured
+// on 2864 products of 1 to 64 rows, 1 to 16384 columns and K from 8 to 65536 in 1 to 128 problems
+// (16-bit and fp32, rows on chunks, words and single elements; the predictions are mostly within
+// 8 to 21 %).  By the predictions 69 of them are more than 5 % slower than with the other
+// kernel.  By size alone, with no look at alignment and rounds, 124 were more than 3 % slower than
+// tiles, up to five times: a long way for few workgroups (54 x 52 x 59410: 148 us, with tiles and 31 slices
+// 32; 64 x 512 x 16384: 27.7 and 19.6) and workgroups in many rounds (125 problems of 56 x 584 x 59:
+// 34.9 and 17.3).  Where no split can be made the tiles' way is as long: two workgroups of 1024 K steps
+// for 16 x 512 x 65536, against 32 of the other kernel.
+struct FewRowsTimes {
+    double first, round;      // us: a call of one round of workgroups, and each further round
+    double unit_bytes_ns;     // bytes a compute unit takes in per ns
+    double bytes_us;          // MB per us from memory
+};
+struct TileTimes {
+    double first, round;      // us: a call of one round of workgroups, and each further round
+    double step, pair_step;   // us of a K step, at one and at two workgroups per compute unit (256x256: always one)
+    double reduce, reduce_mb; // us of a reduction, and per MB of partial sums
+    double bytes_us;
+};
+// 16-bit elements in rows that start on whole 4-byte words, 16-bit ones in others, fp32
+constexpr FewRowsTimes kFewRows[3] = {{4.1, 1.9, 114, 5.0}, {4.5, 3.4, 42, 3.2}, {4.1, 2.4, 65, 4.7}};
+constexpr TileTimes kStagedTiles[3] = {{4.9, 4.3, 0.65, 1.02, 6.2, 2.0, 5.0}, {5.1, 3.8, 0.98, 1.88, 10.4, 0.7, 3.3}, {4.7, 3.0, 2.12, 4.0, 6.0, 1.4, 1.95}};
+constexpr TileTimes kPipeTiles[3] = {{4.3, 14.0, 0.33, 0.55, 4.1, 1.33, 5.0}, {}, {4.2, 2.9, 1.74, 3.5, 5.9, 0.46, 2.1}};  // (whole words always)
+constexpr double kFewRowsMargin = 2.0;  // us by which tiles must be ahead: what a prediction of short calls is worth
+constexpr TileTimes kLargePipeTiles = {7.7, 7.1, 1.05, 1.05, 0.8, 5.0, 3.55};
+
+// `bytes`: operands, once each, and C
+double few_rows_us(const FewRowsTimes& t, int64_t rows, int64_t columns, int waves, int64_t workgroups, int64_t ksteps, double bytes)
+{
+    // workgroups of a compute unit at a time: four waves per SIMD, and their steps in LDS
+    const int64_t lds = waves * (rows + columns) * 128, fit = (160 << 10) / lds;
+    const int64_t resident = fit < 1 ? 1 : fit < 16 / waves ? fit : 16 / waves;
+    const double unit_bytes = static_cast<double>(ceil_div(workgroups, kComputeUnits) * (rows + columns)) * 128.0 * static_cast<double>(ksteps);
+    // (beyond what the memory-side cache can hold from call to call, a compute unit gets 45)
+    const double rate = bytes > 1.2e8 && t.unit_bytes_ns > 45.0 ? 45.0 : t.unit_bytes_ns;
+    const double way = 1e-3 * unit_bytes / rate, all = 1e-6 * bytes / t.bytes_us;
+    return t.first + t.round * static_cast<double>(ceil_div(workgroups, kComputeUnits * resident) - 1) + (way > all ? way : all);
+}
+double tiles_us(const TileTimes& t, bool large, int64_t workgroups, const Slices& slices, double slab_bytes, double bytes)
+{
+    const bool alone = large || workgroups <= kComputeUnits;
+    const double rounds = static_cast<double>(ceil_div(workgroups, (alone ? 1 : 2) * kComputeUnits));
+    double us = t.first + t.round * (rounds - 1.0) + rounds * static_cast<double>(slices.steps) * (alone ? t.step : t.pair_step);
+    if (us < 1e-6 * bytes / t.bytes_us) us = 1e-6 * bytes / t.bytes_us;
+    if (slices.count > 1) us += t.reduce + t.reduce_mb * 1e-6 * slab_bytes * static_cast<double>(slices.count);
+    return us;
+}
+
 // Validates everything, normalises to a row-major C and chooses the launch.
 prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, int64_t K,
                             const void* A, int64_t lda, int64_t strideA, const void* B, int64_t ldb,
@@ -249,32 +297,17 @@ prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, in
                            (p.batch == 1 || p.batch_b % epc == 0);
     const bool pipe_ok = (p.a_vec || a_along_m) && (p.b_vec || b_along_n) && K % step_k == 0 && pitch_ok;
     // ---- few rows: no tile loop and no split, see skinny.hip.  Both operands K-contiguous, K at
-    // least a chunk.  Not for more than 32 rows where 128x128 tiles give half of the compute units a
-    // workgroup, because every 16 or 32 columns read all rows of A again (64 x 16384 x 4096: 39.2 us
-    // with tiles, 41.3 without; 128 problems of 64 x 512 x 512: 24.4 and 38.6), and not where few
-    // workgroups would each have a very long way to go (64 x 512 x 16384, 2.6 MB each: 19.6 us with
-    // tiles and a K split, 27.7 without; 64 x 4096 x 4096, 0.65 MB each: 16.5 and 11.6).
+    // least a chunk; chosen over tiles further down.  Not for more than 32 rows where 128x128 tiles give
+    // half of the compute units a workgroup, because every 16 or 32 columns read all rows of A again
+    // (64 x 16384 x 4096: 39.2 us with tiles, 41.3 without; 128 problems of 64 x 512 x 512: 24.4 and 38.6).
+    // Two blocks of columns where that still gives every compute unit a workgroup.
     const int64_t skinny_m = p.M <= 16 ? 16 : p.M <= 32 ? 32 : 64, skinny_n = ceil_div(p.N, 32) * batch >= kComputeUnits ? 32 : 16;
+    const int64_t skinny_workgroups = ceil_div(p.N, skinny_n) * batch;
+    // as many waves as have K steps of their own, sixteen only where workgroups are few
+    const int skinny_waves = ksteps >= 32 && skinny_workgroups <= kComputeUnits / 2 ? 16 : ksteps >= 8 ? 8 : 4;
     const bool many_tiles = p.M > 32 && pipe_ok && ceil_div(p.N, prism::kStagedTileN) * batch >= kComputeUnits / 2;
-    const bool long_way = ceil_div(p.N, skinny_n) * batch <= kComputeUnits && (skinny_m + skinny_n) * K * ab_esize > kSkinnyBytes && pipe_ok;
-    const bool grid_fits = ceil_div(p.N, skinny_n) * batch <= kSkinnyMaxWorkgroups;
-    if (allow_few_rows && p.M <= kSkinnyRows && a_kfast && b_kfast && K >= epc && pitch_ok && d->split_k <= 1 && hk.pipe_config < 0 &&
-        hk.persistent != 1 && grid_fits && !many_tiles && !long_way) {
-        plan.kernel = 4;
-        plan.tile_m = static_cast<int32_t>(skinny_m);
-        plan.tile_n = static_cast<int32_t>(skinny_n);  // two blocks of columns where that still gives every compute unit a workgroup
-        plan.tile_k = static_cast<int32_t>(step_k);
-        plan.tiles_m = 1;
-        plan.tiles_n = ceil_div(p.N, plan.tile_n);
-        plan.workgroups = plan.tiles_n * batch;
-        // as many waves as have K steps of their own, sixteen only where workgroups are few
-        plan.waves = ksteps >= 32 && plan.workgroups <= kComputeUnits / 2 ? 16 : ksteps >= 8 ? 8 : 4;
-        p.split_k = 1;
-        p.k_slice = p.K;
-        p.tiles_m = 1;
-        p.tiles_n = static_cast<int>(plan.tiles_n);
-        return PRISM_OK;
-    }
+    const bool few_rows = allow_few_rows && p.M <= kSkinnyRows && a_kfast && b_kfast && K >= epc && pitch_ok && d->split_k <= 1 &&
+                          hk.pipe_config < 0 && hk.persistent != 1 && skinny_workgroups <= kSkinnyMaxWorkgroups && !many_tiles;
     int tile_m = prism::kStagedTileM, tile_n = prism::kStagedTileN, waves = prism::kStagedWaves;
     plan.kernel = 1;
     if (pipe_ok) {
@@ -321,6 +354,32 @@ prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, in
         ws_need = slices.count > 1 ? slab_bytes * static_cast<size_t>(slices.count) : 0;
     }
     const int64_t split = slices.count, slice_steps = slices.steps;
+    if (few_rows) {
+        const double bytes = static_cast<double>(ab_esize) * static_cast<double>(K) *
+                                 (static_cast<double>(p.M) * static_cast<double>(p.batch_a == 0 ? 1 : batch) +
+                                  static_cast<double>(p.N) * static_cast<double>(p.batch_b == 0 ? 1 : batch)) +
+                             static_cast<double>(slab_bytes) / 4.0 * c_esize * (p.beta != 0.0f ? 2 : 1);
+        const bool words = aligned(p.A, 4) && aligned(p.B, 4) && p.a_sm % 2 == 0 && p.b_sn % 2 == 0 &&
+                           (batch == 1 || (p.batch_a % 2 == 0 && p.batch_b % 2 == 0));
+        const int kind = ab_esize == 4 ? 2 : words ? 0 : 1;
+        const TileTimes& tiles = plan.kernel == 1 ? kStagedTiles[kind] : tile_m == 256 ? kLargePipeTiles : kPipeTiles[kind];
+        if (few_rows_us(kFewRows[kind], skinny_m, skinny_n, skinny_waves, skinny_workgroups, ksteps, bytes) <=
+            tiles_us(tiles, tile_m == 256, units * split, slices, static_cast<double>(slab_bytes), bytes) + kFewRowsMargin) {
+            plan.kernel = 4;
+            plan.tile_m = static_cast<int32_t>(skinny_m);
+            plan.tile_n = static_cast<int32_t>(skinny_n);
+            plan.tile_k = static_cast<int32_t>(step_k);
+            plan.tiles_m = 1;
+            plan.tiles_n = ceil_div(p.N, skinny_n);
+            plan.workgroups = skinny_workgroups;
+            plan.waves = skinny_waves;
+            p.split_k = 1;
+            p.k_slice = p.K;
+            p.tiles_m = 1;
+            p.tiles_n = static_cast<int>(plan.tiles_n);
+            return PRISM_OK;
+        }
+    }
     p.split_k = static_cast<int>(split);
     p.k_slice = static_cast<int>(slice_steps * step_k);
     p.partial = split > 1 ? static_cast<float*>(d->workspace) : nullptr;

@@ -51,3 +51,9 @@ def test_a_smaller_workspace_holds_fewer_slices(slabs, most, set_hook, capfd):
     set_hook("PRISM_LOG", "1")
     _, split = _split(capfd, 136, 264, 8192, workspace=int(slabs * 136 * 264 * 4))
     assert split == 1 if most == 1 else 1 < split <= most
+
+
+def test_without_room_for_a_split_few_rows_are_not_left_to_tiles(set_hook, capfd):
+    set_hook("PRISM_LOG", "1")
+    assert _split(capfd, 64, 512, 16384) == ("gemm_pipelined", 16)
+    assert _split(capfd, 64, 512, 16384, workspace=0) == ("gemm_skinny", 1)
