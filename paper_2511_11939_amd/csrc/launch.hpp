@@ -28,6 +28,14 @@ hipError_t launch_staged(int ab_dtype, const GemmParams& p, int workgroups, hipS
 hipError_t launch_persistent(int ab_dtype, const GemmParams& p, int total, int workgroups, hipStream_t stream);
 // Few rows: `workgroups` = tiles_n * batch workgroups of `waves` (4, 8 or 16) waves; tile_m (16, 32
 // or 64) covers p.M, tile_n is 16 or 32.
+// A B beyond the memory-side cache (256 MB) cannot be there for the next call either and is read as a
+// stream: 16 x 16384 x 16384 99.6 -> 92.1 us.  Below that a stream loses what the cache would have
+// kept (64 x 4096 x 4096 11.6 -> 14.1 us, 16 x 901 x 5632 7.3 -> 9.4), also when many problems share
+// one B (batch_b == 0; 64 problems of 16 x 4096 x 4096: 158 us, 326 as a stream).
+constexpr bool few_rows_stream_b(int64_t N, int64_t K, int esize, int64_t batch, int64_t batch_b)
+{
+    return static_cast<double>(N) * static_cast<double>(K) * esize * static_cast<double>(batch_b == 0 ? 1 : batch) > 268435456.0;
+}
 hipError_t launch_skinny(int ab_dtype, int tile_m, int tile_n, int waves, const GemmParams& p, int workgroups, hipStream_t stream);
 // Sums the split_k partial slabs in slice order and applies the epilogue; with
 // p.split_k == 0 it writes C <- bias + beta*C (the K == 0 case).

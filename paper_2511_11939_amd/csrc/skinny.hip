@@ -214,11 +214,8 @@ void launch_waves(int waves, const GemmParams& p, int workgroups, hipStream_t st
 {
     if constexpr (NT == 1)  // (two blocks of columns: only with so many workgroups that eight waves do)
         if (waves == 16) return launch<T, MT, NT, 16>(p, workgroups, stream);
-    // A B beyond the memory-side cache (256 MB) cannot be there for the next call either and is
-    // read as a stream: 16 x 16384 x 16384 99.6 -> 92.1 us.  Below that a stream loses what the
-    // cache would have kept (64 x 4096 x 4096 11.6 -> 14.1 us, 16 x 901 x 5632 7.3 -> 9.4).
     if constexpr (NT == 2)
-        if (waves == 8 && static_cast<double>(p.N) * p.K * Frag<T>::kElemBytes * p.batch > 268435456.0) return launch<T, MT, NT, 8, true>(p, workgroups, stream);
+        if (waves == 8 && few_rows_stream_b(p.N, p.K, Frag<T>::kElemBytes, p.batch, p.batch_b)) return launch<T, MT, NT, 8, true>(p, workgroups, stream);
     if (waves == 8) launch<T, MT, NT, 8>(p, workgroups, stream);
     else launch<T, MT, NT, 4>(p, workgroups, stream);
 }

@@ -1,6 +1,10 @@
 """Host-only: which products of few rows take the kernel without tiles.  Problems that one launch of it could
 not take stay on tiles, and so do those that tiles and a split are predicted to be faster at."""
+import os
+import subprocess
+
 import paper_2511_11939_amd as P
+from paper_2511_11939_amd import build
 
 
 def _plan(M, N, K, batch=1, **kw):
@@ -28,3 +32,16 @@ def test_without_a_split_there_is_no_reason_for_tiles():
     assert _plan(64, 512, 16384).split_k > 1
     for M, N, K in ((64, 512, 16384), (16, 512, 65536), (54, 52, 59410)):
         assert _plan(M, N, K, split_k=1).kernel == 4
+
+
+def test_a_shared_b_is_counted_once_before_it_is_read_as_a_stream(tmp_path):
+    source = tmp_path / "rule.hip"
+    source.write_text("""#include "launch.hpp"
+using prism::few_rows_stream_b;
+static_assert(!few_rows_stream_b(4096, 4096, 2, 64, 0), "one B of 33 MB for all problems stays in the caches");
+static_assert(few_rows_stream_b(4096, 4096, 2, 64, 4096 * 4096) && few_rows_stream_b(16384, 16384, 2, 1, 0), "these do not fit");
+static_assert(!few_rows_stream_b(4096, 4096, 2, 8, 4096 * 4096) && few_rows_stream_b(8192, 16384, 4, 9, 0), "at and beyond 256 MB");
+""")
+    r = subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-arch=gfx950", "-std=c++17", "-fsyntax-only",
+                        "--cuda-host-only", "-I", build.CSRC, str(source)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
