@@ -8,10 +8,12 @@ from concurrent.futures import ThreadPoolExecutor
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LIB_PATH = os.path.join(_HERE, "libprism_gemm.so")
-# the same library with a workgroup barrier after every LDS phase of the main loops (race check:
-# its results must equal the normal build's bit for bit)
+# the same library with a workgroup barrier after every LDS phase of the main loops, and a full wait
+# where the lanes of one wave pass data through LDS (race check: its results must equal the normal
+# build's bit for bit)
 PARANOID_LIB_PATH = os.path.join(_HERE, "libprism_gemm_paranoid.so")
 _UNITS = ["kernels.hip", "skinny.hip", "host_api.hip", "scan.hip", "probe.hip"]
+_PARANOID_UNITS = ["kernels.hip", "skinny.hip"]  # the units that have such phases
 _FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
     # keep the compiler from forming packed fp32 vector ops out of scalar float code
@@ -39,22 +41,24 @@ def build(force: bool = False, verbose: bool = False) -> str:
     if not force and not is_stale():
         return LIB_PATH
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    objs = [os.path.join(CSRC, u.replace(".hip", ".o")) for u in _UNITS]
-    paranoid_obj = os.path.join(CSRC, "kernels_paranoid.o")
+    def obj(unit, paranoid=False):
+        return os.path.join(CSRC, unit.replace(".hip", "_paranoid.o" if paranoid else ".o"))
 
-    def compile_one(pair):
-        src, obj = pair
-        extra = ["-DPRISM_PARANOID_BARRIERS"] if obj == paranoid_obj else []
-        cmd = [hipcc, *_FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
+    def compile_one(job):
+        unit, paranoid = job
+        extra = ["-DPRISM_PARANOID_BARRIERS"] if paranoid else []
+        cmd = [hipcc, *_FLAGS, *extra, "-c", os.path.join(CSRC, unit), "-o", obj(unit, paranoid)]
         if verbose:
             print(" ".join(cmd), flush=True)
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
-            raise RuntimeError(f"hipcc failed on {src}:\n{r.stdout}\n{r.stderr}")
+            raise RuntimeError(f"hipcc failed on {unit}:\n{r.stdout}\n{r.stderr}")
 
-    with ThreadPoolExecutor(max_workers=len(_UNITS) + 1) as ex:
-        list(ex.map(compile_one, list(zip(_UNITS, objs)) + [("kernels.hip", paranoid_obj)]))
-    for lib, these in ((LIB_PATH, objs), (PARANOID_LIB_PATH, [paranoid_obj if o.endswith("kernels.o") else o for o in objs])):
+    jobs = [(u, False) for u in _UNITS] + [(u, True) for u in _PARANOID_UNITS]
+    with ThreadPoolExecutor(max_workers=len(jobs)) as ex:
+        list(ex.map(compile_one, jobs))
+    for lib, paranoid in ((LIB_PATH, False), (PARANOID_LIB_PATH, True)):
+        these = [obj(u, paranoid and u in _PARANOID_UNITS) for u in _UNITS]
         cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *these, "-o", lib]
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:

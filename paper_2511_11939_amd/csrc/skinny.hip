@@ -94,6 +94,7 @@ __global__ __launch_bounds__(64 * W, 4) void gemm_skinny(const GemmParams p)
 #pragma unroll
             for (int i = 0; i < MT; ++i) *reinterpret_cast<u32x4*>(put + (NT + i) * BLOCK_BYTES + 8 * r * L::kRowBytes) = a[i][r];
         }
+        wave::lds_in_order(wv);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             frag_t fa[MT], fb[NT];
@@ -106,6 +107,7 @@ __global__ __launch_bounds__(64 * W, 4) void gemm_skinny(const GemmParams p)
 #pragma unroll
                     for (int j = 0; j < NT; ++j) acc[i][j] = wave::mfma_part(wv, fb[j], fa[i], e, acc[i][j]);
         }
+        wave::lds_in_order(wv);
     };
 
     // Whole K steps wave, wave + W, wave + 2 W ...: `mine` of them.

@@ -12,6 +12,18 @@
 namespace prism {
 namespace wave {
 
+// Between a wave's writes to LDS and its reads of what OTHER lanes of the wave wrote, and between those
+// reads and the next writes to the same place.  The LDS takes one wave's accesses in the order in which they
+// were issued, so nothing is waited for and no instruction comes of this; it keeps the compiler, to
+// which a lane's writes and reads look unrelated, from moving one across the other.
+__device__ __forceinline__ void lds_in_order(persp::Wave)
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+#ifdef PRISM_PARANOID_BARRIERS
+    __builtin_amdgcn_s_waitcnt(0);  // every access of the wave has been answered
+#endif
+}
+
 // D[i][j] += sum_k R[i][k] * C[j][k]  for a 16 x 16 block and the k range of one fragment
 // pair (32 k of a 16-bit type, 16 k of fp32).
 // `r` / `c`: each lane's 8 consecutive k of row (lane%16), k-quarter (lane/16).

@@ -116,7 +116,7 @@ __device__ __forceinline__ void drain_direct(persp::Wave, const TileT& acc, Row&
 // row spreads both the writes (16 rows, one piece each) and the reads over all banks.
 constexpr int rows_patch_bytes(int nt) { return lane::kBlock * (2 * lane::kBlock * nt + 16); }
 template <bool PAIRED, int MT, int NT, typename TileT, typename Row, typename Pack, typename Store>
-__device__ __forceinline__ void drain_rows(persp::Wave, const TileT& acc, char* patch, int lane, Row&& row, Pack&& pack, Store&& store)
+__device__ __forceinline__ void drain_rows(persp::Wave wv, const TileT& acc, char* patch, int lane, Row&& row, Pack&& pack, Store&& store)
 {
     static_assert(NT % 2 == 0, "block columns come in pairs");
     constexpr int ROW_BYTES = 2 * lane::kBlock * NT, PITCH = ROW_BYTES + 16;
@@ -140,9 +140,11 @@ __device__ __forceinline__ void drain_rows(persp::Wave, const TileT& acc, char* 
                 *reinterpret_cast<u32x2*>(wr + 64 * s + 32) = b;
             }
         }
+        wave::lds_in_order(wv);
         u32x4 out[ITERS];
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) out[it] = *reinterpret_cast<const u32x4*>(rd + it * ROWS_PER_ITER * PITCH);
+        wave::lds_in_order(wv);
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) store(lane::kBlock * i + it * ROWS_PER_ITER, sub, 16 * piece, out[it]);
         __builtin_amdgcn_sched_barrier(0);  // one block row at a time keeps the register need small

@@ -1,6 +1,7 @@
 """256x256 tiles with operands that are not contiguous along K (row-major B, column-major A, both):
 K loops of one to five steps, sizes that end inside a tile, a wave tile and a block, batches and
-K slices.  Exact on integers, and the race-check build gives the same bits."""
+K slices.  Exact on integers, and the race-check build gives the same bits for a row-major B (for the
+other layouts in test_gpu_race_check_layouts)."""
 import pytest
 
 import paper_2511_11939_amd as P
