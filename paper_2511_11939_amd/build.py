@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import os
 import subprocess
+import sys
 from concurrent.futures import ThreadPoolExecutor
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -53,6 +54,8 @@ def build(force: bool = False, verbose: bool = False) -> str:
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError(f"hipcc failed on {unit}:\n{r.stdout}\n{r.stderr}")
+        if "warning:" in r.stderr:
+            print(r.stderr, file=sys.stderr, flush=True)
 
     jobs = [(u, False) for u in _UNITS] + [(u, True) for u in _PARANOID_UNITS]
     with ThreadPoolExecutor(max_workers=len(jobs)) as ex:

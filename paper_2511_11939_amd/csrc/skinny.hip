@@ -35,6 +35,9 @@ struct Skinny {
     // K steps loaded together (eight rows of a block in each of the two loads): what the registers of two waves per SIMD (W = 16: four) hold twice
     static constexpr int U = MT + NT <= 3 ? 2 : 1;
     static constexpr int THREADS = 64 * W;
+    // waves per SIMD that the registers are meant for: four, or what LDS has room for with 64 rows
+    // by two blocks of columns (two of a workgroup of eight, three of one of four)
+    static constexpr int WAVES_PER_SIMD = MT + NT == 6 ? 2 : 4;
     using frag_t = typename Frag<T>::type;
     struct Steps {
         u32x4 a[U][MT][2], b[U][NT][2];
@@ -42,7 +45,7 @@ struct Skinny {
 };
 
 template <typename T, int MT, int NT, int W, bool STREAM>
-__global__ __launch_bounds__(64 * W, 4) void gemm_skinny(const GemmParams p)
+__global__ __launch_bounds__(64 * W, (Skinny<T, MT, NT, W>::WAVES_PER_SIMD)) void gemm_skinny(const GemmParams p)
 {
     using S = Skinny<T, MT, NT, W>;
     using frag_t = typename S::frag_t;
