@@ -467,9 +467,6 @@ prism_status_t prism_gemm_batched_stamped(const prism_gemm_desc_t* d, int64_t M,
     const prism_status_t s =
         make_problem(d, M, N, K, A, lda, strideA, B, ldb, strideB, C, ldc, strideC, batch, true, &pr);
     if (s != PRISM_OK) return s;
-    // (stamps for fewer workgroups than the kernel for few rows has may be enough for its tiles)
-    if (pr.plan.kernel == 4 && stamps && stamp_bytes < static_cast<size_t>(pr.plan.workgroups) * PRISM_STAMP_BYTES_PER_WORKGROUP)
-        make_problem(d, M, N, K, A, lda, strideA, B, ldb, strideB, C, ldc, strideC, batch, true, &pr, false);
     if (pr.plan.kernel != 2 && pr.plan.kernel != 4) return PRISM_ERR_UNSUPPORTED;  // the others leave no stamps
     if (!stamps || reinterpret_cast<uintptr_t>(stamps) % 8 != 0) return PRISM_ERR_INVALID_ARG;
     if (stamp_bytes < static_cast<size_t>(pr.plan.workgroups) * PRISM_STAMP_BYTES_PER_WORKGROUP) return PRISM_ERR_WORKSPACE;

@@ -45,3 +45,12 @@ static_assert(!few_rows_stream_b(4096, 4096, 2, 8, 4096 * 4096) && few_rows_stre
     r = subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-arch=gfx950", "-std=c++17", "-fsyntax-only",
                         "--cuda-host-only", "-I", build.CSRC, str(source)], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
+
+
+def test_too_few_stamps_are_refused_not_sent_to_another_kernel():
+    """The stamped call is the same launch as the plain one, or none."""
+    desc, base = P.make_desc(), 1 << 40
+    plan = _plan(16, 4096, 4096)
+    args = (desc, 16, 4096, 4096, base, 4096, 0, base << 1, 4096, 0, base << 2, 4096, 0, 1, base << 3)
+    assert plan.kernel == 4
+    assert P.prism_gemm_batched_stamped(*args, plan.workgroups * P.STAMP_BYTES_PER_WORKGROUP - 8) == P.Status.WORKSPACE
