@@ -1,5 +1,6 @@
-"""GPU parity of the single-pass prefix scan (through the C ABI) against the CPU oracle:
-bit-exact, every element."""
+"""GPU parity of the prefix scan (through the C ABI) against the CPU oracle: bit-exact, every element.
+(Up to 2^24 elements the scan runs without a chain of status words; the chain's own edges are in
+test_gpu_scan_look_back.)"""
 import numpy as np
 import pytest
 import torch
@@ -56,9 +57,10 @@ def test_closed_forms_and_wraparound():
 
 
 def test_many_tiles_long_look_back_chain_and_workspace_reuse():
-    """2^24 elements = 1024 tiles (windows of 64 predecessors are walked many times); the same
-    workspace serves three calls in a row, with a shorter problem in between."""
-    n = 1 << 24
+    """Beyond 2^24 elements, where the chain of status words takes over: 1030 tiles (windows of 64
+    predecessors are walked many times); the same workspace serves three calls in a row, with a
+    shorter problem, which needs no chain, in between."""
+    n = (1 << 24) + 5 * TILE + 3
     ws = _ws(n)
     x = scan_input_u32(5, n)
     want = inclusive_scan_u32_ref(x)

@@ -1,6 +1,7 @@
 """The scan entry point that allocates nothing (its status words live in an array of the
 library's code object) against the entry point that takes a workspace: same kernels, so the
-results must be bit-identical; two calls in a row share the array, the second one smaller."""
+results must be bit-identical; two calls in a row share the array, the second one smaller.  (The same
+with the chain of status words: test_gpu_scan_look_back.)"""
 import numpy as np
 import pytest
 import torch
