@@ -29,7 +29,6 @@ struct GemmParams {
     float alpha, beta;
     int c_dtype;          // DT_*
     int bias_along_m;     // 1 when the problem was transposed on the host
-    int a_vec, b_vec;     // operand is K-contiguous with 16-byte aligned rows / chunks
     uint64_t* stamps;     // nullptr, or kStampWords uint64 per workgroup of the main kernel (measurement aid)
 };
 
@@ -132,7 +131,7 @@ template <int OUT>
 __device__ __forceinline__ u32x2 pack4(f32x4 v)
 {
     static_assert(OUT == DT_BF16 || OUT == DT_F16, "16-bit output types");
-    // (as vectors: the compiler then has one conversion instruction per pair of bf16)
+    // round to nearest even (as vectors: the compiler then has one conversion instruction per pair of bf16)
     if constexpr (OUT == DT_BF16) return __builtin_bit_cast(u32x2, __builtin_convertvector(v, bf16x4));
     else return __builtin_bit_cast(u32x2, __builtin_convertvector(v, f16x4));
 }

@@ -274,8 +274,9 @@ prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, in
 
     // ---- alignment facts
     const bool a_kfast = p.a_sk == 1, b_kfast = p.b_sk == 1;
-    p.a_vec = a_kfast && aligned(p.A, 16) && p.a_sm % epc == 0 && (p.batch == 1 || p.batch_a % epc == 0);
-    p.b_vec = b_kfast && aligned(p.B, 16) && p.b_sn % epc == 0 && (p.batch == 1 || p.batch_b % epc == 0);
+    // K-contiguous with 16-byte aligned rows
+    const bool a_vec = a_kfast && aligned(p.A, 16) && p.a_sm % epc == 0 && (p.batch == 1 || p.batch_a % epc == 0);
+    const bool b_vec = b_kfast && aligned(p.B, 16) && p.b_sn % epc == 0 && (p.batch == 1 || p.batch_b % epc == 0);
 
     if (K == 0) {  // C <- bias + beta*C: only the epilogue kernel runs
         plan.kernel = 0;
@@ -295,7 +296,7 @@ prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, in
                            (p.batch == 1 || p.batch_a % epc == 0);
     const bool b_along_n = p.b_sn == 1 && p.b_sk != 1 && aligned(p.B, 16) && p.b_sk % epc == 0 && p.N % epc == 0 &&
                            (p.batch == 1 || p.batch_b % epc == 0);
-    const bool pipe_ok = (p.a_vec || a_along_m) && (p.b_vec || b_along_n) && K % step_k == 0 && pitch_ok;
+    const bool pipe_ok = (a_vec || a_along_m) && (b_vec || b_along_n) && K % step_k == 0 && pitch_ok;
     // ---- few rows: no tile loop and no split, see skinny.hip.  Both operands K-contiguous, K at
     // least a chunk; chosen over tiles further down.  Not for more than 32 rows where 128x128 tiles give
     // half of the compute units a workgroup, because every 16 or 32 columns read all rows of A again
@@ -322,13 +323,13 @@ prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, in
             // from 3072^3 on and on 1024x1024x32768.
             // (operands that are not contiguous along K: see large_k_row_tiles)
             const int64_t big = ceil_div(p.M, 256) * ceil_div(p.N, 256) * batch;
-            if (p.a_vec && p.b_vec) cfg = (big >= kComputeUnits / 2 || ksteps >= kVeryLongK) ? 0 : 1;
+            if (a_vec && b_vec) cfg = (big >= kComputeUnits / 2 || ksteps >= kVeryLongK) ? 0 : 1;
             else cfg = large_k_row_tiles(p.M, p.N, batch, ksteps, d->split_k) ? 0 : 1;
         }
         // an operand that is not K-contiguous is kept as k-rows in LDS, with either tile
-        if (!p.a_vec || !p.b_vec) cfg = (cfg == 0 ? 9 : 2) + (!p.a_vec ? (!p.b_vec ? 2 : 1) : 0);
+        if (!a_vec || !b_vec) cfg = (cfg == 0 ? 9 : 2) + (!a_vec ? (!b_vec ? 2 : 1) : 0);
         // fp32 operands: 128x128 tiles in all four layout pairs
-        if (ab_esize == 4) cfg = 5 + (p.b_vec ? 0 : 1) + (p.a_vec ? 0 : 2);
+        if (ab_esize == 4) cfg = 5 + (b_vec ? 0 : 1) + (a_vec ? 0 : 2);
         out->pipe_config = cfg;
         tile_m = prism::kPipeConfigs[cfg].tile_m;
         tile_n = prism::kPipeConfigs[cfg].tile_n;

@@ -128,15 +128,7 @@ __host__ __device__ constexpr int acc_first_col(int j, int lane)
     return PAIRED ? 32 * (j >> 1) + 8 * (lane >> 4) + 4 * (j & 1) : kBlock * j + 4 * (lane >> 4);
 }
 
-// ---- output conversion ---------------------------------------------------------
-__device__ __forceinline__ uint16_t to_bf16_bits(float x)
-{
-    return __builtin_bit_cast(uint16_t, static_cast<__bf16>(x));  // round to nearest even
-}
-__device__ __forceinline__ uint16_t to_f16_bits(float x)
-{
-    return __builtin_bit_cast(uint16_t, static_cast<_Float16>(x));  // round to nearest even
-}
+// ---- values of C read back ---------------------------------------------------------
 __device__ __forceinline__ float from_bf16_bits(uint16_t h)
 {
     return __builtin_bit_cast(float, static_cast<uint32_t>(h) << 16);

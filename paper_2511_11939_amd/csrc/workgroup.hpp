@@ -530,8 +530,8 @@ struct Pipeline {
 // (code appendix, `while(true)` over tiles) with the loads of the next tile pipelined
 // under the tail of the current one.
 //
-// LDS: two operand slots (128 KiB) and, behind them, one 8 KiB epilogue patch per wave,
-// which together are exactly the 160 KiB of a compute unit; the patches are separate so
+// LDS: two operand slots (128 KiB) and, behind them, one epilogue patch of 4352 bytes per wave,
+// 145 of the 160 KiB of a compute unit together; the patches are separate so
 // that the epilogue of a tile can run while the slots already hold the next tile.
 // ------------------------------------------------------------------------------------
 template <typename T, int HEADN = 0>  // copies of a step left for the start of the next one (0: measured best)
@@ -892,11 +892,13 @@ struct Staged {
     static constexpr int b_slot(int s) { return 2 * A::BYTES + s * B::BYTES; }
     static constexpr int LDS_BYTES = 2 * (A::BYTES + B::BYTES);
     static_assert(NW * rows_patch_bytes(NT) <= LDS_BYTES, "epilogue patches reuse the operand slots");
+    static_assert(WTM % 64 == 0 && WTN % 64 == 0, "wave tiles start at whole groups of 64 elements");
 
     using tile_t = wave::Tile<T, MT, NT>;
     using frag_t = typename Frag<T>::type;
 
-    // One operand's fragments of a sub-step: NBLK blocks of 16 rows from row `first` of the tile.
+    // One operand's fragments of a sub-step: NBLK blocks of 16 rows from row `first` of the tile (the
+    // first row of a wave tile, a multiple of 64).
     template <int EXT, bool K_ROWS, int NBLK>
     __device__ __forceinline__ static void read(persp::Wave wv, frag_t (&f)[NBLK], const char* slot, int first, int ks, int lane)
     {
@@ -904,19 +906,14 @@ struct Staged {
         if constexpr (!K_ROWS) {
             wave::load_fragments<T, 64, NBLK>(wv, f, slot, first, ks, lane);
         } else if constexpr (ES == 2) {
-            // (the lane parts take four blocks of 16, 64 elements, from a multiple of 64: a 32-wide
-            // wave tile in the upper half of such a group starts at the third block)
+            static_assert(NBLK % 4 == 0, "the lane parts take four blocks of 16, 64 elements, from a multiple of 64");
             uint32_t part[4];
 #pragma unroll
             for (int jl = 0; jl < 4; ++jl) part[jl] = wave::k_rows_lane_part<ROW_BYTES>(wv, jl, lane);
-            const int group = first & ~63, block = (first & 63) / lane::kBlock;
 #pragma unroll
             for (int j = 0; j < NBLK; ++j) {
-                uint32_t at[4];
-#pragma unroll
-                for (int jl = 0; jl < 4; ++jl) at[jl] = NBLK >= 4 || block == 0 ? part[jl] : part[(jl + 2) & 3];
-                const wave::v4s lo = wave::read_k_rows_half<ROW_BYTES>(wv, slot, group, j, ks, 0, at);
-                const wave::v4s hi = wave::read_k_rows_half<ROW_BYTES>(wv, slot, group, j, ks, 1, at);
+                const wave::v4s lo = wave::read_k_rows_half<ROW_BYTES>(wv, slot, first, j, ks, 0, part);
+                const wave::v4s hi = wave::read_k_rows_half<ROW_BYTES>(wv, slot, first, j, ks, 1, part);
                 f[j] = __builtin_bit_cast(frag_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
             }
         } else {
