@@ -245,7 +245,7 @@ PRISM_API int prism_version(void);
 /*
  * The library reads its test and experiment hooks from the environment once, at the first call
  * that needs them, and keeps them: PRISM_GEMM_CONFIG=0|1 (pin 256x256 / 128x128 tiles of the
- * pipeline), PRISM_PERSISTENT=0|1 (never / whenever possible use the persistent kernel),
+ * pipeline, few rows or not), PRISM_PERSISTENT=0|1 (never / whenever possible use the persistent kernel),
  * PRISM_LOG=1 (one line per launch on stderr: problem, kernel, tile, split),
  * PRISM_SCAN_SPIN_LIMIT=<polls> (bound of the scan's look-back wait).  This call reads them
  * again, for a process that changes its environment after the first call (tests do).

@@ -57,7 +57,7 @@ bool overlaps(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes)
 
 // Hooks for tests and experiments, read from the environment once (at the first call that
 // needs them, or again on prism_reread_environment) and kept:
-//   PRISM_GEMM_CONFIG=<index>  pins the pipeline's tile configuration (0: 256x256, 1: 128x128), few rows or not
+//   PRISM_GEMM_CONFIG=0|1      pins the pipeline's tile (0: 256x256, 1: 128x128) and keeps few rows on tiles
 //   PRISM_PERSISTENT=0|1       never / whenever possible use the persistent kernel
 //   PRISM_LOG=1                one line per launch on stderr: problem, kernel, tile, split
 struct Hooks {
@@ -74,7 +74,7 @@ void load_hooks_locked()
     Hooks h;
     if (const char* e = std::getenv("PRISM_GEMM_CONFIG"); e && *e) {
         const int v = std::atoi(e);
-        if (v >= 0 && v < prism::kNumPipeConfigs) h.pipe_config = v;
+        if (v == 0 || v == 1) h.pipe_config = v;  // (others name nothing)
     }
     if (const char* e = std::getenv("PRISM_PERSISTENT"); e && (e[0] == '0' || e[0] == '1')) h.persistent = e[0] - '0';
     if (const char* e = std::getenv("PRISM_LOG"); e && e[0] == '1') h.log = true;
@@ -314,7 +314,6 @@ prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, in
     if (pipe_ok) {
         plan.kernel = 2;
         int cfg = hk.pipe_config;
-        if (cfg > 1) cfg = -1;  // the hook names a tile size (0: 256x256, 1: 128x128)
         if (cfg < 0) {
             // Big tiles when they give at least half of the compute units a workgroup, or for a
             // very long K (the split then needs fewer slices); else small tiles, two workgroups

@@ -54,3 +54,9 @@ def test_too_few_stamps_are_refused_not_sent_to_another_kernel():
     args = (desc, 16, 4096, 4096, base, 4096, 0, base << 1, 4096, 0, base << 2, 4096, 0, 1, base << 3)
     assert plan.kernel == 4
     assert P.prism_gemm_batched_stamped(*args, plan.workgroups * P.STAMP_BYTES_PER_WORKGROUP - 8) == P.Status.WORKSPACE
+
+
+def test_a_hook_that_names_no_tile_changes_nothing(set_hook):
+    for value, kernel in (("0", 2), ("1", 2), ("2", 4), ("11", 4)):
+        set_hook("PRISM_GEMM_CONFIG", value)
+        assert _plan(16, 4096, 4096).kernel == kernel, value
