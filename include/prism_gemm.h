@@ -119,7 +119,10 @@ typedef struct prism_gemm_plan {
  * elements (64 of a 16-bit type, 32 of fp32) and, for an operand that is not
  * contiguous along K (column-major A, row-major B), M respectively N is a
  * multiple of 16 bytes of elements; everything else runs on a staged kernel
- * with the same arithmetic.  For a fixed problem, descriptor and GPU the result is
+ * with the same arithmetic.  When both operands are contiguous along K, a C (or
+ * C^T, for a column-major C) of up to 64 rows runs, at any alignment, on a kernel
+ * of its own without tiles and without a split wherever that is expected to be
+ * faster.  For a fixed problem, descriptor and GPU the result is
  * bit-for-bit reproducible: split-K partial sums are reduced in slice order.
  */
 PRISM_API prism_status_t prism_gemm(const prism_gemm_desc_t* d, int64_t M, int64_t N, int64_t K,
@@ -153,7 +156,8 @@ PRISM_API prism_status_t prism_gemm_workspace_size(const prism_gemm_desc_t* d, i
 /*
  * The launch plan for a problem, with the same validation and choices as
  * prism_gemm_batched (pointer alignment is taken from the pointers given; pass
- * the real device pointers or NULL to assume 16-byte alignment).  Host only.
+ * the real device pointers or NULL to assume 16-byte alignment; a workspace of the
+ * size wanted is assumed, whatever the descriptor holds).  Host only.
  */
 PRISM_API prism_status_t prism_gemm_plan(const prism_gemm_desc_t* d, int64_t M, int64_t N, int64_t K,
                                const void* A, int64_t lda, int64_t strideA,

@@ -1,15 +1,20 @@
 /*
- * prism_scan.h -- C ABI of the single-pass prefix scan on one MI355X (gfx950).
+ * prism_scan.h -- C ABI of the prefix scan on one MI355X (gfx950).
  *
  * The paper's second benchmark (section 6.1): the inclusive prefix sum of an
  * array of 32-bit unsigned integers,
  *
  *     out[i] = (in[0] + in[1] + ... + in[i]) mod 2^32,
  *
- * computed in ONE pass over the data with the decoupled look-back scheme the
- * paper implements (every tile publishes its aggregate, then looks back over
- * the tiles before it until it meets one whose full prefix is known).  The
- * data is read once and written once: 8 bytes of HBM traffic per element.
+ * Beyond 2^24 elements it is computed in ONE pass over the data with the
+ * decoupled look-back scheme the paper implements (every tile publishes its
+ * aggregate, then looks back over the tiles before it until it meets one whose
+ * full prefix is known): the data is read once and written once, 8 bytes of HBM
+ * traffic per element.  Up to 2^24 elements, which the caches hold, there is no
+ * chain of tiles to wait for: one workgroup scans up to 32768 elements alone, and
+ * above that a first launch sums every tile and a second one scans the tiles (the
+ * data is read twice, the second time from the caches).  The results are the same
+ * whole numbers either way.
  *
  * Ownership, streams and errors as in prism_gemm.h: device pointers belong to
  * the caller, the library allocates nothing, calls enqueue work on the given
@@ -27,8 +32,8 @@ extern "C" {
 
 /*
  * Bytes of device workspace a scan of n elements needs (tile counter, error
- * word and one 8-byte status word per tile of 16384 elements).  n < 0 is
- * PRISM_ERR_INVALID_ARG.  Host arithmetic only.
+ * word and 8 bytes per 16384 elements: the status word of a tile, or the sums of
+ * two half as long).  n < 0 is PRISM_ERR_INVALID_ARG.  Host arithmetic only.
  */
 PRISM_API prism_status_t prism_scan_workspace_size(int64_t n, size_t* bytes_out);
 
@@ -37,8 +42,9 @@ PRISM_API prism_status_t prism_scan_workspace_size(int64_t n, size_t* bytes_out)
  *
  * in, out      device, 4-byte aligned; out may be the same pointer as in (the
  *              scan then works in place, as the paper's kernel does); any other
- *              overlap is PRISM_ERR_INVALID_ARG.  16-byte aligned pointers take
- *              the vector path, others a slower element-wise one.
+ *              overlap is PRISM_ERR_INVALID_ARG.  Beyond 2^24 elements 16-byte
+ *              aligned pointers take the vector path, others a slower
+ *              element-wise one; up to there the alignment does not matter.
  * n            number of elements, 0 <= n < 2^43; n == 0 launches nothing.
  * workspace    device, 8-byte aligned, at least prism_scan_workspace_size(n)
  *              bytes (else PRISM_ERR_WORKSPACE); it is initialised by the call
@@ -46,7 +52,7 @@ PRISM_API prism_status_t prism_scan_workspace_size(int64_t n, size_t* bytes_out)
  *              Calls that overlap in time need separate workspaces.
  * hip_stream   a hipStream_t passed as void*; NULL is the default stream.
  *
- * A tile waits for the tiles before it with a bounded number of polls; if the
+ * Beyond 2^24 elements a tile waits for the tiles before it with a bounded number of polls; if the
  * bound is ever hit (it is not in a working system: tiles take their numbers
  * from an atomic counter, so every tile waited for is already running) the
  * kernel still terminates, the result is wrong, and prism_scan_check reports it.

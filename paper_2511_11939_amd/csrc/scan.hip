@@ -1,6 +1,7 @@
-// Single-pass inclusive prefix sum over uint32 with decoupled look-back (the paper's scan
+// Inclusive prefix sum over uint32: in a single pass with decoupled look-back (the paper's scan
 // benchmark, section 6.1 and its code appendix `scan_kernel`; the scheme is Merrill and
-// Garland's).  Layered like the GEMM code: lane-level sums of four consecutive elements,
+// Garland's) where the data comes from memory, without a chain of tiles where the caches hold it
+// (further down).  Layered like the GEMM code: lane-level sums of four consecutive elements,
 // a wave-level scan with cross-lane moves, a workgroup-level combine through LDS, and a
 // grid-level chain of per-tile status words.
 //
