@@ -84,25 +84,30 @@ __global__ __launch_bounds__(64 * W, (Skinny<T, MT, NT, W>::WAVES_PER_SIMD)) voi
     }
     char* slot = lds + wave * WAVE_BYTES;
     char* put = slot + L::offset(lane >> 3, chunk);  // (rows l / 8 and l / 8 + 8 have the same swizzle)
+    const char* passed = slot + wave::unknown_offset(wv);
     f32x4 acc[MT][NT];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     auto multiply = [&](const u32x4 (&a)[MT][2], const u32x4 (&b)[NT][2]) __attribute__((always_inline)) {
+        // (B's first fragments are read while the loads of A may still be on their way)
+        frag_t fa[MT], fb[NT];
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
+        for (int j = 0; j < NT; ++j)
 #pragma unroll
-            for (int j = 0; j < NT; ++j) *reinterpret_cast<u32x4*>(put + j * BLOCK_BYTES + 8 * r * L::kRowBytes) = b[j][r];
+            for (int r = 0; r < 2; ++r) *reinterpret_cast<u32x4*>(put + j * BLOCK_BYTES + 8 * r * L::kRowBytes) = b[j][r];
+        PRISM_PARANOID_WAIT();
+        wave::load_fragments<T, 64, NT>(wv, fb, passed, 0, 0, lane);
 #pragma unroll
-            for (int i = 0; i < MT; ++i) *reinterpret_cast<u32x4*>(put + (NT + i) * BLOCK_BYTES + 8 * r * L::kRowBytes) = a[i][r];
-        }
-        wave::lds_in_order(wv);
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int r = 0; r < 2; ++r) *reinterpret_cast<u32x4*>(put + (NT + i) * BLOCK_BYTES + 8 * r * L::kRowBytes) = a[i][r];
+        PRISM_PARANOID_WAIT();
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            frag_t fa[MT], fb[NT];
-            wave::load_fragments<T, 64, NT>(wv, fb, slot, 0, h, lane);
-            wave::load_fragments<T, 64, MT>(wv, fa, slot + NT * BLOCK_BYTES, 0, h, lane);
+            if (h > 0) wave::load_fragments<T, 64, NT>(wv, fb, passed, 0, h, lane);
+            wave::load_fragments<T, 64, MT>(wv, fa, passed + NT * BLOCK_BYTES, 0, h, lane);
 #pragma unroll
             for (int e = 0; e < wave::mfma_parts(frag_t{}); ++e)
 #pragma unroll
@@ -110,7 +115,7 @@ __global__ __launch_bounds__(64 * W, (Skinny<T, MT, NT, W>::WAVES_PER_SIMD)) voi
 #pragma unroll
                     for (int j = 0; j < NT; ++j) acc[i][j] = wave::mfma_part(wv, fb[j], fa[i], e, acc[i][j]);
         }
-        wave::lds_in_order(wv);
+        PRISM_PARANOID_WAIT();
     };
 
     // Whole K steps wave, wave + W, wave + 2 W ...: `mine` of them.

@@ -12,17 +12,23 @@
 namespace prism {
 namespace wave {
 
-// Between a wave's writes to LDS and its reads of what OTHER lanes of the wave wrote, and between those
-// reads and the next writes to the same place.  The LDS takes one wave's accesses in the order in which they
-// were issued, so nothing is waited for and no instruction comes of this; it keeps the compiler, to
-// which a lane's writes and reads look unrelated, from moving one across the other.
-__device__ __forceinline__ void lds_in_order(persp::Wave)
+// Zero, for the addresses of the reads of a wave that passes values from lane to lane through LDS.  The
+// LDS takes one wave's accesses in the order in which they were issued, so nothing has to be waited
+// for; but to the compiler a lane's reads, at addresses it can tell from those the lane writes to, are
+// unrelated to its writes and may move across them.  With an offset of which it knows nothing the
+// reads may be of anything, and they keep their place.
+__device__ __forceinline__ int unknown_offset(persp::Wave)
 {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-#ifdef PRISM_PARANOID_BARRIERS
-    __builtin_amdgcn_s_waitcnt(0);  // every access of the wave has been answered
-#endif
+    int zero = 0;
+    asm volatile("" : "+s"(zero));
+    return zero;
 }
+// Race check of such passes: in the build with full barriers every access has been answered here.
+#ifdef PRISM_PARANOID_BARRIERS
+#define PRISM_PARANOID_WAIT() __builtin_amdgcn_s_waitcnt(0)
+#else
+#define PRISM_PARANOID_WAIT() do { } while (0)
+#endif
 
 // D[i][j] += sum_k R[i][k] * C[j][k]  for a 16 x 16 block and the k range of one fragment
 // pair (32 k of a 16-bit type, 16 k of fp32).

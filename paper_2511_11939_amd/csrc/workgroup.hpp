@@ -124,7 +124,7 @@ __device__ __forceinline__ void drain_rows(persp::Wave wv, const TileT& acc, cha
     constexpr int ROWS_PER_ITER = 64 / PIECES, ITERS = lane::kBlock / ROWS_PER_ITER;
     char* wr = patch + (lane & 15) * PITCH + (PAIRED ? 16 : 8) * (lane >> 4);
     const int piece = lane % PIECES, sub = lane / PIECES;
-    const char* rd = patch + sub * PITCH + 16 * piece;
+    const char* rd = patch + wave::unknown_offset(wv) + sub * PITCH + 16 * piece;
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
         row(i);
@@ -140,11 +140,11 @@ __device__ __forceinline__ void drain_rows(persp::Wave wv, const TileT& acc, cha
                 *reinterpret_cast<u32x2*>(wr + 64 * s + 32) = b;
             }
         }
-        wave::lds_in_order(wv);
+        PRISM_PARANOID_WAIT();
         u32x4 out[ITERS];
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) out[it] = *reinterpret_cast<const u32x4*>(rd + it * ROWS_PER_ITER * PITCH);
-        wave::lds_in_order(wv);
+        PRISM_PARANOID_WAIT();
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) store(lane::kBlock * i + it * ROWS_PER_ITER, sub, 16 * piece, out[it]);
         __builtin_amdgcn_sched_barrier(0);  // one block row at a time keeps the register need small

@@ -13,20 +13,18 @@ extern "C" __global__ void passes(int* out)
 {
     __shared__ int lds[65];
     const persp::Wave wv = persp::Grid::at_kernel_entry().workgroup<64>().wave();
-    const int lane = threadIdx.x & 63;
-    const int before = lds[lane + 1];
-    %s;
+    const int lane = threadIdx.x & 63, reader = lane + %s;
+    const int before = lds[reader + 1];
     lds[lane] = lane;
-    %s;
-    out[lane] = lds[lane + 1];
+    out[lane] = lds[reader + 1];
     out[64 + lane] = before;
 }
 """
 
 
-def _lds_accesses(tmp_path, between):
+def _lds_accesses(tmp_path, reader):
     source, asm = tmp_path / "passes.hip", tmp_path / "passes.s"
-    source.write_text(SOURCE % (between, between))
+    source.write_text(SOURCE % reader)
     r = subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-arch=gfx950", "-O3", "-std=c++17", "-S",
                         "--cuda-device-only", "-I", build.CSRC, str(source), "-o", str(asm)], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
@@ -34,11 +32,12 @@ def _lds_accesses(tmp_path, between):
 
 
 def test_a_wave_reads_again_what_other_lanes_have_written(tmp_path):
-    assert _lds_accesses(tmp_path, "wave::lds_in_order(wv)") == ["read", "write", "read"]
+    assert _lds_accesses(tmp_path, "wave::unknown_offset(wv)") == ["read", "write", "read"]
 
 
 def test_the_kernels_that_pass_values_this_way_say_so():
-    """The kernel for few rows (a step, and the reads before the next step) and the epilogue's patch."""
-    assert open(os.path.join(build.CSRC, "skinny.hip")).read().count("wave::lds_in_order(wv)") == 2
-    assert open(os.path.join(build.CSRC, "workgroup.hpp")).read().count("wave::lds_in_order(wv)") == 2
+    """The kernel for few rows and the epilogue's patch; both units are in the race-check build."""
+    for unit, waits in (("skinny.hip", 3), ("workgroup.hpp", 2)):
+        source = open(os.path.join(build.CSRC, unit)).read()
+        assert source.count("wave::unknown_offset(wv)") == 1 and source.count("PRISM_PARANOID_WAIT()") == waits, unit
     assert {"kernels.hip", "skinny.hip"} <= set(build._PARANOID_UNITS)
