@@ -363,8 +363,14 @@ prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, in
                            (batch == 1 || (p.batch_a % 2 == 0 && p.batch_b % 2 == 0));
         const int kind = ab_esize == 4 ? 2 : words ? 0 : 1;
         const TileTimes& tiles = plan.kernel == 1 ? kStagedTiles[kind] : tile_m == 256 ? kLargePipeTiles : kPipeTiles[kind];
+        // The times were taken on operands that the memory-side cache holds in part.  From memory a tile's
+        // K step takes longer, most where every tile has a compute unit to itself (8 x 15702 x 2816: 36.6 us
+        // with 123 tiles, 21.7 without), so tiles must be ahead by half there and by a fifth elsewhere;
+        // not so for a long way of few workgroups, 1.5 MB each, measured both ways.
+        const bool long_way = skinny_workgroups <= kComputeUnits && (skinny_m + skinny_n) * K * ab_esize > (3 << 19) && slices.count > 1;
+        const double ahead = long_way ? 1.0 : plan.kernel == 2 && slices.count == 1 ? 1.5 : 1.2;
         if (few_rows_us(kFewRows[kind], skinny_m, skinny_n, skinny_waves, skinny_workgroups, ksteps, bytes) <=
-            tiles_us(tiles, tile_m == 256, units * split, slices, static_cast<double>(slab_bytes), bytes) + kFewRowsMargin) {
+            ahead * tiles_us(tiles, tile_m == 256, units * split, slices, static_cast<double>(slab_bytes), bytes) + kFewRowsMargin) {
             plan.kernel = 4;
             plan.tile_m = static_cast<int32_t>(skinny_m);
             plan.tile_n = static_cast<int32_t>(skinny_n);

@@ -25,6 +25,8 @@ def test_a_long_way_for_few_workgroups_is_split_whatever_the_alignment():
         plan = _plan(54, 52, K)
         assert plan.kernel in (1, 2) and plan.split_k >= 8, K
     assert _plan(56, 584, 59, batch=125).kernel == 1          # many rounds of short loops
+    for M, N, K in ((8, 15702, 2816), (6, 15232, 3072)):      # half the compute units, operands from memory
+        assert _plan(M, N, K).kernel == 4
     assert _plan(54, 52, 2000).kernel == 4 and _plan(16, 4096, 4096).kernel == 4
 
 
