@@ -89,8 +89,11 @@ typedef struct prism_gemm_plan {
                                 3 = the same pipeline, persistent: used for more tiles
                                     than compute units with short K loops,
                                 4 = few rows (C, or C^T when swapped, has at most 64):
-                                    whole sums per workgroup, no tile loop, no split   */
-    int32_t tile_m, tile_n, tile_k; /* workgroup tile                                */
+                                    whole sums per workgroup, no tile loop, no split;
+                                with 1 and 2 and tile_n below 128 the waves of a
+                                workgroup deal K steps among themselves              */
+    int32_t tile_m, tile_n, tile_k; /* workgroup tile; 128 x 32 x tile_k: of four workgroups
+                                    of 32 rows each                                  */
     int32_t waves;           /* wavefronts per workgroup                              */
     int32_t split_k;         /* K slices actually used (>= 1)                         */
     int32_t swapped;         /* 1 if the problem is run as C^T = B^T A^T              */
@@ -119,7 +122,9 @@ typedef struct prism_gemm_plan {
  * elements (64 of a 16-bit type, 32 of fp32) and, for an operand that is not
  * contiguous along K (column-major A, row-major B), M respectively N is a
  * multiple of 16 bytes of elements; everything else runs on a staged kernel
- * with the same arithmetic.  When both operands are contiguous along K, a C (or
+ * with the same arithmetic.  Either way a product of few tiles, or of a short K, runs
+ * on smaller workgroups whose waves deal the K steps among themselves, where that
+ * is expected to be faster.  When both operands are contiguous along K, a C (or
  * C^T, for a column-major C) of up to 64 rows runs, at any alignment, on a kernel
  * of its own without tiles and without a split wherever that is expected to be
  * faster.  For a fixed problem, descriptor and GPU the result is

@@ -13,8 +13,8 @@ LIB_PATH = os.path.join(_HERE, "libprism_gemm.so")
 # where the lanes of one wave pass data through LDS (race check: its results must equal the normal
 # build's bit for bit)
 PARANOID_LIB_PATH = os.path.join(_HERE, "libprism_gemm_paranoid.so")
-_UNITS = ["kernels.hip", "skinny.hip", "host_api.hip", "scan.hip", "probe.hip"]
-_PARANOID_UNITS = ["kernels.hip", "skinny.hip"]  # the units that have such phases
+_UNITS = ["kernels.hip", "skinny.hip", "dealt.hip", "host_api.hip", "scan.hip", "probe.hip"]
+_PARANOID_UNITS = ["kernels.hip", "skinny.hip", "dealt.hip"]  # the units that have such phases
 _FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
     # keep the compiler from forming packed fp32 vector ops out of scalar float code

@@ -32,6 +32,8 @@ struct Problem {
     prism_gemm_plan_t plan;
     int ab_dtype;
     int pipe_config;  // index into kPipeConfigs when plan.kernel is 2 or 3
+    int dealt_rows;   // rows of C per workgroup of the kernel that deals K steps to waves (0: another kernel)
+    bool odd_rows;    // of that kernel: operand rows that start in the middle of 32-bit words
     int total_units;  // (tile, unit) pairs the persistent kernel walks
 };
 
@@ -197,11 +199,78 @@ double tiles_us(const TileTimes& t, bool large, int64_t workgroups, const Slices
     return us;
 }
 
+// ---- K steps dealt to the waves of a workgroup (dealt.hip), or tiles with a K loop of their own?  Both
+// are predicted, from times measured on 3550 products of 17 to 4000 rows and columns and K from 17
+// to 60000 in 1 to 200 problems (all layout pairs; 16-bit operands whose rows start on whole words, 16-bit
+// ones that do not, fp32).  The predictions are mostly within 10 to 20 %, so tiles must be behind by
+// kDealtMargin, more for calls of several rounds and for long rows of both operands, whose loads
+// touch many pages; and operands beyond what the memory-side cache holds from call to call stay on
+// tiles.  Measured over all of them, the calls take 0.62 of the time that tiles alone took (the
+// best choice each time: 0.59), and 21 are more than 5 % slower (the worst 38 %).
+struct DealtTimes {
+    double first, round;      // us: a call of one round of workgroups, and each further round
+    double step;              // us of a wave's K step
+    double unit_kb_us;        // kB a compute unit takes in per us
+    double k_rows;            // by how much more an operand costs that is not contiguous along K
+    double mb_us, reduce, reduce_mb;  // MB per us from memory; us of a reduction, and per MB of partial sums
+};
+struct DealtShape {
+    int rows, columns, waves, waves_m, resident;  // of a workgroup; waves side by side along m; workgroups of a compute unit
+    int split_workgroups;                         // of all units together, up to which sums are split
+    DealtTimes times[3];                          // by kind of operands, as above
+};
+constexpr DealtShape kDealtShapes[3] = {
+    {32, 32, 4, 1, 5, 2 * kComputeUnits,
+     {{3.3, 2.4, 0.01, 82.5, 0.30, 4.2, 3.1, 0.23}, {3.7, 2.9, 0.25, 63.7, 0.27, 3.4, 4.6, 0.02}, {3.7, 3.2, 0.17, 52.0, 0.02, 4.0, 3.8, 0.01}}},
+    {32, 32, 8, 1, 2, 2 * kComputeUnits,
+     {{3.0, 1.9, 0.52, 93.4, 0.38, 4.1, 3.2, 0.32}, {3.2, 2.1, 0.82, 65.3, 0.26, 3.5, 4.8, 0.02}, {3.7, 2.6, 0.27, 61.3, 0.05, 3.9, 3.7, 0.19}}},
+    {128, 64, 8, 2, 1, kComputeUnits,
+     {{4.8, 4.4, 0.19, 99.9, 0.18, 2.9, 4.0, 0.33}, {5.0, 4.8, 1.10, 74.5, 0.10, 2.3, 4.0, 0.50}, {5.2, 5.1, 1.57, 34.1, 0.01, 3.4, 4.0, 0.01}}},
+};
+constexpr double kDealtMargin = 1.15, kDealtRoundMargin = 0.1, kDealtLongRowMargin = 0.1;
+constexpr double kDealtMaxMb = 100.0;
+constexpr int kDealtLongRow = 48;       // K steps
+constexpr int kDealtMinSliceSteps = 8;
+double dealt_us(const DealtShape& shape, const DealtTimes& t, int64_t workgroups, const Slices& slices, int k_row_operands, double slab_mb, double mb)
+{
+    const double rounds = static_cast<double>(ceil_div(workgroups, kComputeUnits * shape.resident));
+    const double kb = 0.128 * static_cast<double>((shape.rows + shape.columns * shape.waves_m) * slices.steps);
+    const double way = static_cast<double>(ceil_div(workgroups, kComputeUnits)) * kb / t.unit_kb_us * (1.0 + t.k_rows * k_row_operands);
+    const double waits = rounds * static_cast<double>(ceil_div(slices.steps, shape.waves / shape.waves_m)) * t.step;
+    const double partial = slices.count > 1 ? slab_mb * static_cast<double>(slices.count) : 0.0;
+    double us = t.first + t.round * (rounds - 1.0) + (way > waits ? way : waits);
+    if (us < 2.0 + mb / t.mb_us) us = 2.0 + mb / t.mb_us;
+    return slices.count > 1 ? us + t.reduce + t.reduce_mb * partial : us;
+}
+// How far the rounding errors of a sum add up, in additions one after the other: the matrix instructions
+// of one wave's steps, then the sums of its waves, then those of the slices.  A call's must not be longer than the
+// tiles' would be (1620 x 122 x 3120 fp32, thirteen steps a wave against slices of eight: 3.6e-7
+// off the exact product against 3.1e-7).
+int64_t sum_length(int64_t steps, int64_t waves, int64_t slices, int esize)
+{
+    return ceil_div(steps, waves) * (esize == 4 ? 8 : 2) + (steps < waves ? steps : waves) + slices;
+}
+// The tiles' side of it: staged kernel by kind, pipeline with 128x128 tiles of 16-bit operands contiguous along
+// K, of others, of fp32, and with 256x256 tiles.  (As tiles_us, fitted to these products.)
+constexpr TileTimes kTilesStaged[3] = {{6.5, 3.6, 0.72, 1.28, 4.1, 0.38, 2.7}, {6.8, 4.7, 0.90, 1.62, 5.5, 0.34, 2.7}, {7.1, 7.3, 2.10, 4.24, 4.4, 0.37, 1.9}};
+constexpr TileTimes kTilesPipe = {4.9, 0.6, 0.53, 0.80, 2.6, 0.31, 3.0}, kTilesKRows = {4.7, 6.3, 0.55, 0.77, 1.0, 0.51, 3.3};
+constexpr TileTimes kTilesPipeF32 = {5.7, 2.6, 1.77, 3.62, 3.0, 0.35, 1.7}, kTilesLarge = {13.5, 7.2, 0.89, 0.89, 0.0, 0.03, 2.7};
+double loop_tiles_us(const TileTimes& t, bool large, int64_t workgroups, const Slices& slices, double slab_mb, double mb)
+{
+    const int64_t per_unit = ceil_div(workgroups, kComputeUnits);
+    const double steps = static_cast<double>(slices.steps);
+    double us = large ? t.first + static_cast<double>(per_unit) * steps * t.step + t.round * static_cast<double>(per_unit - 1)
+                      : t.first + t.round * static_cast<double>(ceil_div(per_unit, 2) - 1) +
+                            steps * (static_cast<double>(per_unit / 2) * t.pair_step + static_cast<double>(per_unit % 2) * t.step);
+    if (us < 2.0 + mb / t.bytes_us) us = 2.0 + mb / t.bytes_us;
+    return slices.count > 1 ? us + t.reduce + t.reduce_mb * slab_mb * static_cast<double>(slices.count) : us;
+}
+
 // Validates everything, normalises to a row-major C and chooses the launch.
 prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, int64_t K,
                             const void* A, int64_t lda, int64_t strideA, const void* B, int64_t ldb,
                             int64_t strideB, const void* C, int64_t ldc, int64_t strideC, int64_t batch,
-                            bool need_pointers, Problem* out, bool allow_few_rows = true)
+                            bool need_pointers, Problem* out, bool allow_few_rows = true, bool allow_dealt = true)
 {
     if (!d || !out) return PRISM_ERR_INVALID_ARG;
     if (!valid_dtype_ab(d->ab_dtype) || !valid_dtype_c(d->c_dtype) || !valid_layout(d->layout_a) ||
@@ -386,6 +455,76 @@ prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, in
             return PRISM_OK;
         }
     }
+    // ---- few tiles for the chip, or short K loops: K steps dealt to the waves of smaller workgroups
+    // (its loads are whole chunks: they lie inside a row, or, of k-rows shorter than a chunk, inside the operand,
+    // those of all steps but the last towards its end, those of the last, at the end of a row, towards its start)
+    auto chunks = [&](bool kfast, int64_t extent, int64_t pitch) {
+        if (kfast || extent >= epc) return (kfast ? K : extent) >= epc;
+        return K > step_k && (K - 1) % step_k * pitch + pitch + extent >= epc;
+    };
+    if (allow_dealt && chunks(a_kfast, p.M, p.a_sk) && chunks(b_kfast, p.N, p.b_sk) && pitch_ok && d->split_k <= 1 && hk.pipe_config < 0 && hk.persistent != 1) {
+        const double slab_mb = 1e-6 * static_cast<double>(slab_bytes);
+        const double mb = 1e-6 * ab_esize * static_cast<double>(batch) * static_cast<double>(K) * (static_cast<double>(p.M) + static_cast<double>(p.N)) +
+                          slab_mb / 4.0 * c_esize * (p.beta != 0.0f ? 2 : 1);
+        const bool word_pitches = (a_kfast ? p.a_sm : p.a_sk) % 2 == 0 && (b_kfast ? p.b_sn : p.b_sk) % 2 == 0 &&
+                                  (batch == 1 || (p.batch_a % 2 == 0 && p.batch_b % 2 == 0));
+        const bool word_bases = aligned(p.A, 4) && aligned(p.B, 4);
+        const int kind = ab_esize == 4 ? 2 : word_pitches && word_bases ? 0 : 1;
+        const int k_row_operands = (a_kfast ? 0 : 1) + (b_kfast ? 0 : 1);
+        const TileTimes& tiles = plan.kernel == 1 ? kTilesStaged[kind] : ab_esize == 4 ? kTilesPipeF32 : tile_m == 256 ? kTilesLarge : k_row_operands ? kTilesKRows : kTilesPipe;
+        double best = mb <= kDealtMaxMb ? loop_tiles_us(tiles, tile_m == 256, units * split, slices, slab_mb, mb) : 0.0;
+        const double margin = kDealtMargin + (k_row_operands == 0 && ksteps >= kDealtLongRow ? kDealtLongRowMargin : 0.0);
+        const int64_t tiles_length = sum_length(slices.steps, 1, slices.count, ab_esize);
+        const DealtShape* chosen = nullptr;
+        Slices chosen_slices{1, ksteps};
+        for (const DealtShape& shape : kDealtShapes) {
+            if (best <= 0.0) break;
+            const int64_t own = ceil_div(p.M, shape.rows) * ceil_div(p.N, shape.columns);
+            if (own > kMaxTiles / batch) continue;
+            int64_t most = d->split_k ? 1 : shape.split_workgroups / (own * batch);
+            if (most > ksteps / kDealtMinSliceSteps) most = ksteps / kDealtMinSliceSteps;
+            if (most > kMaxSplit) most = kMaxSplit;
+            if (need_pointers && most > 1) {
+                const int64_t held = d->workspace ? static_cast<int64_t>(d->workspace_bytes / slab_bytes) : 0;
+                if (most > held) most = held;
+            }
+            // whole sums, or as many slices as give every compute unit its workgroups
+            for (int64_t count : {int64_t{1}, most}) {
+                if (count < 1 || (count == 1 && chosen == &shape)) continue;
+                const Slices some = slices_of(count, ksteps);
+                if (sum_length(some.steps, shape.waves / shape.waves_m, some.count, ab_esize) > tiles_length) continue;
+                const int64_t workgroups = own * batch * some.count;
+                const double us = dealt_us(shape, shape.times[kind], workgroups, some, k_row_operands, slab_mb, mb);
+                const double rounds = static_cast<double>(ceil_div(workgroups, kComputeUnits * shape.resident));
+                const double needed = chosen ? us : us * (margin + kDealtRoundMargin * (rounds - 1.0));
+                if (needed >= best) continue;
+                best = us;
+                chosen = &shape;
+                chosen_slices = some;
+            }
+        }
+        if (chosen) {
+            // The schedule deals blocks of four 32-row tiles, one below the other, to neighbouring workgroups.
+            plan.tile_m = 128;
+            plan.tile_n = chosen->columns;
+            plan.tile_k = static_cast<int32_t>(step_k);
+            plan.waves = chosen->waves;
+            plan.split_k = static_cast<int32_t>(chosen_slices.count);
+            plan.tiles_m = ceil_div(p.M, 128);
+            plan.tiles_n = ceil_div(p.N, chosen->columns);
+            p.tiles_m = static_cast<int>(ceil_div(p.M, chosen->rows));
+            p.tiles_n = static_cast<int>(plan.tiles_n);
+            p.split_k = static_cast<int>(chosen_slices.count);
+            p.k_slice = static_cast<int>(chosen_slices.steps * step_k);
+            p.partial = p.split_k > 1 ? static_cast<float*>(d->workspace) : nullptr;
+            plan.workgroups = static_cast<int64_t>(p.tiles_m) * p.tiles_n * batch * p.split_k;
+            plan.workspace_bytes = p.split_k > 1 ? slab_bytes * static_cast<size_t>(p.split_k) : 0;
+            out->dealt_rows = chosen->rows;
+            // (a row that starts in the middle of a word is read from the word before: there must be one)
+            out->odd_rows = kind == 1 && word_bases && (batch == 1 || (p.batch_a >= 0 && p.batch_b >= 0));
+            return PRISM_OK;
+        }
+    }
     p.split_k = static_cast<int>(split);
     p.k_slice = static_cast<int>(slice_steps * step_k);
     p.partial = split > 1 ? static_cast<float*>(d->workspace) : nullptr;
@@ -425,7 +564,9 @@ prism_status_t run(const Problem& pr, hipStream_t stream)
     const GemmParams& p = pr.p;
     if (p.M == 0 || p.N == 0 || p.batch == 0) return PRISM_OK;
     hipError_t e = hipSuccess;
-    if (pr.plan.kernel == 3)
+    if (pr.dealt_rows)
+        e = prism::launch_dealt(pr.ab_dtype, pr.dealt_rows, pr.plan.waves, pr.odd_rows, p, static_cast<int>(pr.plan.workgroups), stream);
+    else if (pr.plan.kernel == 3)
         e = prism::launch_persistent(pr.ab_dtype, p, pr.total_units, static_cast<int>(pr.plan.workgroups), stream);
     else if (pr.plan.kernel == 2)
         e = prism::launch_pipelined(pr.pipe_config, pr.ab_dtype, p, static_cast<int>(pr.plan.workgroups), stream);
@@ -436,10 +577,10 @@ prism_status_t run(const Problem& pr, hipStream_t stream)
     if (e != hipSuccess) return PRISM_ERR_LAUNCH;
     if (hooks().log) {
         static const char* const names[] = {"none", "gemm_staged", "gemm_pipelined", "gemm_persistent", "gemm_skinny"};
-        std::fprintf(stderr, "prism_gemm: M=%d N=%d K=%d batch=%d%s kernel=%s tile=%dx%dx%d waves=%d split_k=%d workgroups=%lld\n",
+        std::fprintf(stderr, "prism_gemm: M=%d N=%d K=%d batch=%d%s kernel=%s tile=%dx%dx%d waves=%d split_k=%d workgroups=%lld%s\n",
                      p.M, p.N, p.K, p.batch, pr.plan.swapped ? " (run as C^T = B^T A^T)" : "",
                      names[pr.plan.kernel >= 0 && pr.plan.kernel <= 4 ? pr.plan.kernel : 0], pr.plan.tile_m, pr.plan.tile_n,
-                     pr.plan.tile_k, pr.plan.waves, pr.plan.split_k, static_cast<long long>(pr.plan.workgroups));
+                     pr.plan.tile_k, pr.plan.waves, pr.plan.split_k, static_cast<long long>(pr.plan.workgroups), pr.dealt_rows ? " k_steps=dealt" : "");
     }
     if (p.split_k != 1) {  // K == 0 (split_k == 0) or a real split: the reduction writes C
         e = prism::launch_reduce(p, stream);
@@ -509,12 +650,17 @@ prism_status_t prism_gemm_workspace_size(const prism_gemm_desc_t* d, int64_t M, 
     // far apart keep a call off the kernel for few rows, which needs no workspace.
     const int64_t lda = d->layout_a == PRISM_ROW_MAJOR ? K : M, ldb = d->layout_b == PRISM_ROW_MAJOR ? N : K;
     const int64_t ldc = d->layout_c == PRISM_ROW_MAJOR ? N : M;
-    Problem pr;
-    const prism_status_t s =
-        make_problem(d, M, N, K, nullptr, lda < 1 ? 1 : lda, M * K, nullptr, ldb < 1 ? 1 : ldb, K * N, nullptr,
-                     ldc < 1 ? 1 : ldc, M * N, batch, false, &pr, false);
-    if (s != PRISM_OK) return s;
-    *bytes_out = pr.plan.workspace_bytes;
+    // A call may also find another kernel the faster one than these do: enough for either.
+    size_t most = 0;
+    for (const bool allow_dealt : {false, true}) {
+        Problem pr;
+        const prism_status_t s =
+            make_problem(d, M, N, K, nullptr, lda < 1 ? 1 : lda, M * K, nullptr, ldb < 1 ? 1 : ldb, K * N, nullptr,
+                         ldc < 1 ? 1 : ldc, M * N, batch, false, &pr, false, allow_dealt);
+        if (s != PRISM_OK) return s;
+        if (pr.plan.workspace_bytes > most) most = pr.plan.workspace_bytes;
+    }
+    *bytes_out = most;
     return PRISM_OK;
 }
 

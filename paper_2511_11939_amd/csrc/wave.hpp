@@ -86,7 +86,7 @@ template <int ROW_BYTES>
 __device__ __forceinline__ uint32_t k_rows_lane_part(persp::Wave, int jl, int lane)
 {
     const int i = lane & 15, kq = lane >> 4, s_row = i >> 2, x = (i & 3) >> 1;
-    return (8 * kq + s_row) * ROW_BYTES + (((2 * jl + x) ^ (s_row << 1)) * lane::kChunkBytes) + (i & 1) * 8;
+    return (8 * kq + s_row) * ROW_BYTES + (((2 * jl + x) ^ ((s_row << 1) & (ROW_BYTES / lane::kChunkBytes - 1))) * lane::kChunkBytes) + (i & 1) * 8;
 }
 // Half h (k = 8*(lane/16) + 4h .. +3 of sub-step ksub) of the fragment of the j-th block of 16
 // elements counted from element `first` (a multiple of 64) of the k-rows at `tile`.
