@@ -34,7 +34,19 @@
 namespace prism {
 namespace {
 
-using u16_alias = uint16_t __attribute__((may_alias));
+// Rows of 16-bit elements may start in the middle of a 32-bit word.  The vector memory unit takes a 16-byte load from
+// there in pieces: 38 bytes a ns and compute unit (60 where every other row is such a one) against 110 for loads
+// at whole words.  So a chunk is loaded from the word that it starts in, and put in place, `shift`
+// (0 or 2) bytes further down, with the first word of the next lane's, which holds the chunk behind
+// it; the last chunk of a row lacks its last element.
+__device__ __forceinline__ u32x4 chunk_in_place(u32x4 v, uint32_t shift)
+{
+    constexpr int kRowShl1 = 0x101;  // from the next lane of 16
+    const uint32_t next = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v[0]), kRowShl1, 0xF, 0xF, true));
+    return u32x4{__builtin_amdgcn_alignbyte(v[1], v[0], shift), __builtin_amdgcn_alignbyte(v[2], v[1], shift),
+                 __builtin_amdgcn_alignbyte(v[3], v[2], shift), __builtin_amdgcn_alignbyte(next, v[3], shift)};
+}
+using u16_alias = uint16_t __attribute__((may_alias));  // (an element of what was written as chunks)
 
 // What one wave does with one operand: 16 * BLK rows (m or n) of a K step (128 bytes of k).
 // K-contiguous rows become the 128-byte rows of TileLayout, an operand contiguous along its other
@@ -142,13 +154,7 @@ struct WaveOperand {
     {
         if constexpr (ODD) {
 #pragma unroll
-            for (int r = 0; r < LOADS; ++r) {
-                const u32x4 v = regs[r];
-                const uint32_t next = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v[0]), 0x101, 0xF, 0xF, true));
-                *reinterpret_cast<u32x4*>(slot + put[r & 1] + 1024 * r) =
-                    u32x4{__builtin_amdgcn_alignbyte(v[1], v[0], shift), __builtin_amdgcn_alignbyte(v[2], v[1], shift),
-                          __builtin_amdgcn_alignbyte(v[3], v[2], shift), __builtin_amdgcn_alignbyte(next, v[3], shift)};
-            }
+            for (int r = 0; r < LOADS; ++r) *reinterpret_cast<u32x4*>(slot + put[r & 1] + 1024 * r) = chunk_in_place(regs[r], shift);
             *reinterpret_cast<u16_alias*>(slot + last_put) = static_cast<uint16_t>(last);
         } else {
 #pragma unroll

@@ -200,13 +200,13 @@ double tiles_us(const TileTimes& t, bool large, int64_t workgroups, const Slices
 }
 
 // ---- K steps dealt to the waves of a workgroup (dealt.hip), or tiles with a K loop of their own?  Both
-// are predicted, from times measured on 3550 products of 17 to 4000 rows and columns and K from 17
+// are predicted, from times measured on 3400 products of 17 to 4000 rows and columns and K from 17
 // to 60000 in 1 to 200 problems (all layout pairs; 16-bit operands whose rows start on whole words, 16-bit
 // ones that do not, fp32).  The predictions are mostly within 10 to 20 %, so tiles must be behind by
 // kDealtMargin, more for calls of several rounds and for long rows of both operands, whose loads
 // touch many pages; and operands beyond what the memory-side cache holds from call to call stay on
-// tiles.  Measured over all of them, the calls take 0.62 of the time that tiles alone took (the
-// best choice each time: 0.59), and 21 are more than 5 % slower (the worst 38 %).
+// tiles.  Measured over all of them, the calls take 0.69 of the time that tiles alone take (the
+// best choice each time: 0.66), and 24 are more than 5 % slower (the worst 32 %).
 struct DealtTimes {
     double first, round;      // us: a call of one round of workgroups, and each further round
     double step;              // us of a wave's K step
@@ -221,11 +221,11 @@ struct DealtShape {
 };
 constexpr DealtShape kDealtShapes[3] = {
     {32, 32, 4, 1, 5, 2 * kComputeUnits,
-     {{3.3, 2.4, 0.01, 82.5, 0.30, 4.2, 3.1, 0.23}, {3.7, 2.9, 0.25, 63.7, 0.27, 3.4, 4.6, 0.02}, {3.7, 3.2, 0.17, 52.0, 0.02, 4.0, 3.8, 0.01}}},
+     {{3.4, 2.3, 0.05, 81.3, 0.29, 4.0, 3.3, 0.05}, {3.8, 2.8, 0.01, 65.4, 0.27, 3.4, 4.8, 0.01}, {3.9, 3.1, 0.01, 52.5, 0.02, 4.0, 4.2, 0.01}}},
     {32, 32, 8, 1, 2, 2 * kComputeUnits,
-     {{3.0, 1.9, 0.52, 93.4, 0.38, 4.1, 3.2, 0.32}, {3.2, 2.1, 0.82, 65.3, 0.26, 3.5, 4.8, 0.02}, {3.7, 2.6, 0.27, 61.3, 0.05, 3.9, 3.7, 0.19}}},
+     {{3.0, 1.8, 0.59, 90.7, 0.36, 4.1, 3.4, 0.16}, {3.3, 2.0, 0.82, 68.0, 0.27, 5.3, 5.3, 0.01}, {3.8, 2.6, 0.27, 60.1, 0.04, 3.1, 4.3, 0.12}}},
     {128, 64, 8, 2, 1, kComputeUnits,
-     {{4.8, 4.4, 0.19, 99.9, 0.18, 2.9, 4.0, 0.33}, {5.0, 4.8, 1.10, 74.5, 0.10, 2.3, 4.0, 0.50}, {5.2, 5.1, 1.57, 34.1, 0.01, 3.4, 4.0, 0.01}}},
+     {{5.1, 4.3, 0.01, 92.6, 0.08, 2.9, 2.6, 0.26}, {5.7, 4.9, 0.01, 71.0, 0.05, 2.7, 3.6, 0.17}, {5.5, 4.6, 1.67, 34.1, 0.01, 2.0, 4.3, 0.34}}},
 };
 constexpr double kDealtMargin = 1.15, kDealtRoundMargin = 0.1, kDealtLongRowMargin = 0.1;
 constexpr double kDealtMaxMb = 100.0;
@@ -252,9 +252,9 @@ int64_t sum_length(int64_t steps, int64_t waves, int64_t slices, int esize)
 }
 // The tiles' side of it: staged kernel by kind, pipeline with 128x128 tiles of 16-bit operands contiguous along
 // K, of others, of fp32, and with 256x256 tiles.  (As tiles_us, fitted to these products.)
-constexpr TileTimes kTilesStaged[3] = {{6.5, 3.6, 0.72, 1.28, 4.1, 0.38, 2.7}, {6.8, 4.7, 0.90, 1.62, 5.5, 0.34, 2.7}, {7.1, 7.3, 2.10, 4.24, 4.4, 0.37, 1.9}};
-constexpr TileTimes kTilesPipe = {4.9, 0.6, 0.53, 0.80, 2.6, 0.31, 3.0}, kTilesKRows = {4.7, 6.3, 0.55, 0.77, 1.0, 0.51, 3.3};
-constexpr TileTimes kTilesPipeF32 = {5.7, 2.6, 1.77, 3.62, 3.0, 0.35, 1.7}, kTilesLarge = {13.5, 7.2, 0.89, 0.89, 0.0, 0.03, 2.7};
+constexpr TileTimes kTilesStaged[3] = {{6.3, 5.0, 0.54, 1.16, 3.9, 0.39, 2.9}, {6.4, 4.6, 0.73, 1.40, 4.6, 0.37, 2.4}, {6.1, 7.2, 1.88, 3.85, 5.7, 0.34, 2.4}};
+constexpr TileTimes kTilesPipe = {4.6, 3.0, 0.54, 0.68, 1.6, 0.45, 2.8}, kTilesKRows = {4.5, 3.8, 0.55, 0.79, 1.6, 0.41, 3.3};
+constexpr TileTimes kTilesPipeF32 = {5.4, 6.6, 1.78, 3.77, 3.0, 0.26, 2.2}, kTilesLarge = {7.2, 7.4, 1.03, 1.03, 0.0, 1.37, 2.3};
 double loop_tiles_us(const TileTimes& t, bool large, int64_t workgroups, const Slices& slices, double slab_mb, double mb)
 {
     const int64_t per_unit = ceil_div(workgroups, kComputeUnits);

@@ -86,6 +86,17 @@ __device__ __forceinline__ void copy_async_16(persp::Wave, const char* uniform_b
 // Every lane holds four consecutive columns of one row per block: row 16 i + lane % 16 of the
 // wave tile, columns lane::acc_first_col<PAIRED>(j, lane) and on.  Two ways out:
 //
+// A block's values are taken from the accumulators at this place and no earlier: without it the moves of
+// all blocks drift to the top of the epilogue and spill.  Tiles of 16 blocks leave it to the compiler where
+// they are: asked for in the accumulation registers, they would halve the others (128 of 256 at two
+// waves per SIMD), which the staged loop's steps on their way and two sets of fragments need.
+template <int BLOCKS>
+__device__ __forceinline__ void taken_here(f32x4& v)
+{
+    if constexpr (BLOCKS > 16) asm volatile("" : "+a"(v));
+    else asm volatile("" : "+v"(v));
+}
+
 // drain_direct (32-bit results): the four values go straight out, 64 contiguous bytes of a row
 // (PAIRED: 128 in two instructions) from the four lanes that share it.
 // row(i) is called before the blocks of block row i, put(i, j, values) for each of them.
@@ -97,10 +108,8 @@ __device__ __forceinline__ void drain_direct(persp::Wave, const TileT& acc, Row&
         row(i);
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
-            // (taken from the accumulation registers here and no earlier: without this the moves
-            // of all blocks drift to the top of the epilogue and spill)
             f32x4 v = acc.acc[i][j];
-            asm volatile("" : "+a"(v));
+            taken_here<MT * NT>(v);
             put(i, j, v);
         }
         __builtin_amdgcn_sched_barrier(0);  // one block row at a time keeps the register need small
@@ -131,7 +140,8 @@ __device__ __forceinline__ void drain_rows(persp::Wave wv, const TileT& acc, cha
 #pragma unroll
         for (int s = 0; s < NT / 2; ++s) {
             f32x4 lo = acc.acc[i][2 * s], hi = acc.acc[i][2 * s + 1];
-            asm volatile("" : "+a"(lo), "+a"(hi));  // taken from the accumulation registers here and no earlier
+            taken_here<MT * NT>(lo);
+            taken_here<MT * NT>(hi);
             const u32x2 a = pack(i, 2 * s, lo), b = pack(i, 2 * s + 1, hi);
             if constexpr (PAIRED) {
                 *reinterpret_cast<u32x4*>(wr + 64 * s) = u32x4{a[0], a[1], b[0], b[1]};
@@ -730,12 +740,15 @@ struct PersistentPipe {
 // from the transposing reads (wave::read_k_rows_half; fp32: four 4-byte reads).  Either way a
 // thread moves whole 16-byte chunks.
 //
-// What bounds it: the time from a load to its use, at one or two workgroups per compute unit.
-// So two K steps are in flight in registers beside the two in LDS (a load issued in step t is
-// written to LDS in step t + 2 and used in step t + 3), and a step has one barrier.  Measured:
-// 1999 x 2001 x 1003 bf16, odd pitches, 24.2 us (131.8 us with element loads for every unaligned
-// chunk and one LDS slot); 960 x 3072 x 3733, row-major B, 53 us (329); 4 x 978 x 10368, column-major A,
-// row-major B, 118 us (364 without anything in flight, as is still done where a step is the only one).
+// What bounds it: the time from a load to its use, at one or two workgroups per compute unit, and then the
+// LDS, which takes every step's 32 KiB in and gives 64 out.  So two K steps are in flight in
+// registers beside the two in LDS (a load issued in step t is written to LDS in step t + 2 and used
+// in step t + 3), and a step has one barrier and nothing that waits for it: reads, writes and loads stand
+// between the matrix instructions as in Pipeline, with the next sub-step's fragments already in registers.
+// Measured: 1999 x 2001 x 1003 bf16, odd pitches, 21.2 -> 17.0 us (reads, matrix instructions and
+// writes one after the other before), 1999 x 2001 x 1004 18.2 -> 15.8, 3001 x 2003 x 1005 fp32 134 -> 122.
+// Rows at odd elements loaded in whole words and moved into place, as in dealt.hip, cost more here than their
+// slower loads do (18.6 us).
 //
 // Only the last K step can hold k beyond the matrix or read past an operand's last element.  It
 // is computed first and takes the careful fetch: chunks are loaded from where they lie wholly inside their row and
@@ -822,16 +835,22 @@ struct StagedOperand {
         return !K_ROWS || !narrow || k_left * pitch + rows * ES >= lane::kChunkBytes;
     }
 
+    __device__ __forceinline__ global_bytes step_base(int k0) const
+    {
+        return (global_bytes)scalarize(tile + (K_ROWS ? k0 * pitch : static_cast<int64_t>(k0) * ES));
+    }
+    __device__ __forceinline__ void fetch_one(int i, u32x4 (&regs)[CHUNKS], global_bytes step)
+    {
+        // (seen as a fresh 32-bit value, so that the load takes it as its offset register
+        // beside the uniform base instead of a 64-bit sum kept per chunk)
+        asm volatile("" : "+v"(off[i]));
+        regs[i] = *(const __attribute__((address_space(1))) u32x4_any*)(step + off[i]);
+    }
     __device__ __forceinline__ void fetch(u32x4 (&regs)[CHUNKS], int k0)
     {
-        const global_bytes step = (global_bytes)scalarize(tile + (K_ROWS ? k0 * pitch : static_cast<int64_t>(k0) * ES));
+        const global_bytes step = step_base(k0);
 #pragma unroll
-        for (int i = 0; i < CHUNKS; ++i) {
-            // (seen as a fresh 32-bit value, so that the load takes it as its offset register
-            // beside the uniform base instead of a 64-bit sum kept per chunk)
-            asm volatile("" : "+v"(off[i]));
-            regs[i] = *(const __attribute__((address_space(1))) u32x4_any*)(step + off[i]);
-        }
+        for (int i = 0; i < CHUNKS; ++i) fetch_one(i, regs, step);
     }
     template <bool MAYBE_NARROW>
     __device__ __forceinline__ void fetch_careful(u32x4 (&regs)[CHUNKS], int k0, int k_end) const
@@ -871,10 +890,14 @@ struct StagedOperand {
                 if (k0 + tile_row(i) >= k_end) regs[i] = u32x4{0u, 0u, 0u, 0u};
         }
     }
+    __device__ __forceinline__ void commit_one(int i, const u32x4 (&regs)[CHUNKS], char* slot) const
+    {
+        *reinterpret_cast<u32x4*>(slot + lds_off + i * ROW_STEP * ROW_BYTES) = regs[i];
+    }
     __device__ __forceinline__ void commit(const u32x4 (&regs)[CHUNKS], char* slot) const
     {
 #pragma unroll
-        for (int i = 0; i < CHUNKS; ++i) *reinterpret_cast<u32x4*>(slot + lds_off + i * ROW_STEP * ROW_BYTES) = regs[i];
+        for (int i = 0; i < CHUNKS; ++i) commit_one(i, regs, slot);
     }
 };
 
@@ -897,34 +920,25 @@ struct Staged {
     using tile_t = wave::Tile<T, MT, NT>;
     using frag_t = typename Frag<T>::type;
 
-    // One operand's fragments of a sub-step: NBLK blocks of 16 rows from row `first` of the tile (the
-    // first row of a wave tile, a multiple of 64).
-    template <int EXT, bool K_ROWS, int NBLK>
-    __device__ __forceinline__ static void read(persp::Wave wv, frag_t (&f)[NBLK], const char* slot, int first, int ks, int lane)
+    // The fragment of block j (16 rows) of a sub-step, from row `first` of the tile (the first row of a wave
+    // tile, a multiple of 64); `part`: the lane parts of a 16-bit operand's k-rows.
+    template <int EXT, bool K_ROWS>
+    __device__ __forceinline__ static frag_t read(persp::Wave wv, const char* slot, int first, int j, int ks, int lane, const uint32_t (&part)[4])
     {
         constexpr int ROW_BYTES = EXT * ES;
         if constexpr (!K_ROWS) {
-            wave::load_fragments<T, 64, NBLK>(wv, f, slot, first, ks, lane);
+            return lane::load_fragment<T, 64>(wv.lane(), slot, first + lane::kBlock * j, ks, lane);
         } else if constexpr (ES == 2) {
-            static_assert(NBLK % 4 == 0, "the lane parts take four blocks of 16, 64 elements, from a multiple of 64");
-            uint32_t part[4];
-#pragma unroll
-            for (int jl = 0; jl < 4; ++jl) part[jl] = wave::k_rows_lane_part<ROW_BYTES>(wv, jl, lane);
-#pragma unroll
-            for (int j = 0; j < NBLK; ++j) {
-                const wave::v4s lo = wave::read_k_rows_half<ROW_BYTES>(wv, slot, first, j, ks, 0, part);
-                const wave::v4s hi = wave::read_k_rows_half<ROW_BYTES>(wv, slot, first, j, ks, 1, part);
-                f[j] = __builtin_bit_cast(frag_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-            }
+            const wave::v4s lo = wave::read_k_rows_half<ROW_BYTES>(wv, slot, first, j, ks, 0, part);
+            const wave::v4s hi = wave::read_k_rows_half<ROW_BYTES>(wv, slot, first, j, ks, 1, part);
+            return __builtin_bit_cast(frag_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
         } else {
-            const int x = lane & 15, g = lane >> 4;
+            const int x = lane & 15, g = lane >> 4, n = first + lane::kBlock * j + x;
+            const char* src = slot + (16 * ks + 4 * g) * ROW_BYTES + (((n >> 2) ^ ((g & 1) << 2)) * lane::kChunkBytes) + (n & 3) * 4;
+            frag_t f;
 #pragma unroll
-            for (int j = 0; j < NBLK; ++j) {
-                const int n = first + lane::kBlock * j + x;
-                const char* src = slot + (16 * ks + 4 * g) * ROW_BYTES + (((n >> 2) ^ ((g & 1) << 2)) * lane::kChunkBytes) + (n & 3) * 4;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) f[j][e] = *reinterpret_cast<const float*>(src + e * ROW_BYTES);
-            }
+            for (int e = 0; e < 4; ++e) f[e] = *reinterpret_cast<const float*>(src + e * ROW_BYTES);
+            return f;
         }
     }
 
@@ -961,18 +975,32 @@ struct Staged {
             a.commit(ra[set], lds + a_slot(slot));
             b.commit(rb[set], lds + b_slot(slot));
         };
+        uint32_t part_a[4] = {}, part_b[4] = {};
+        if constexpr (ES == 2) {
+#pragma unroll
+            for (int jl = 0; jl < 4; ++jl) {
+                if constexpr (A_MK) part_a[jl] = wave::k_rows_lane_part<BM * ES>(wv, jl, lane);
+                if constexpr (B_KN) part_b[jl] = wave::k_rows_lane_part<BN * ES>(wv, jl, lane);
+            }
+        }
+        constexpr int PARTS = wave::mfma_parts(frag_t{}), NM = MT * NT * PARTS, NR = MT + NT;
+        frag_t fa[2][MT], fb[2][NT];
+        // fragment number r of sub-step ks: a0, all b, remaining a (what the first matrix instructions need first)
+        auto read_one = [&](int r, int buf, int slot, int ks) __attribute__((always_inline)) {
+            if (r == 0 || r > NT) fa[buf][r == 0 ? 0 : r - NT] = read<BM, A_MK>(wv, lds + a_slot(slot), a_row0, r == 0 ? 0 : r - NT, ks, lane, part_a);
+            else fb[buf][r - 1] = read<BN, B_KN>(wv, lds + b_slot(slot), b_row0, r - 1, ks, lane, part_b);
+        };
+        auto mfma = [&](int m, int buf) __attribute__((always_inline)) {
+            const int e = m / (MT * NT), blk = m % (MT * NT), i = blk / NT, j = blk % NT;
+            acc.acc[i][j] = wave::mfma_part(wv, fb[buf][j], fa[buf][i], e, acc.acc[i][j]);
+        };
         auto compute = [&](int slot) __attribute__((always_inline)) {
 #pragma unroll
             for (int ks = 0; ks < KSUB; ++ks) {
-                frag_t fa[MT], fb[NT];
-                read<BM, A_MK, MT>(wv, fa, lds + a_slot(slot), a_row0, ks, lane);
-                read<BN, B_KN, NT>(wv, fb, lds + b_slot(slot), b_row0, ks, lane);
 #pragma unroll
-                for (int e = 0; e < wave::mfma_parts(frag_t{}); ++e)
+                for (int r = 0; r < NR; ++r) read_one(r, ks, slot, ks);
 #pragma unroll
-                    for (int i = 0; i < MT; ++i)
-#pragma unroll
-                        for (int j = 0; j < NT; ++j) acc.acc[i][j] = wave::mfma_part(wv, fb[j], fa[i], e, acc.acc[i][j]);
+                for (int m = 0; m < NM; ++m) mfma(m, ks);
             }
         };
         // my LDS reads and writes are done; loads into registers stay in flight across the barrier
@@ -1019,22 +1047,49 @@ struct Staged {
         hand_over();
         compute(1);
         hand_over();
-        // Step t computes from slot t % 2 while step t + 1 goes from its registers into the other
-        // slot (everybody left that slot at the last barrier) and step t + 3 sets out into the
-        // registers so freed.  (An odd last step is followed by one that computes nothing: the
-        // loop keeps one way through its loads, so that each wait counts exactly.)
+        // Step t computes from slot t % 2.  Its first sub-step's matrix instructions have between them the reads of the
+        // second's fragments and the writes of step t + 1, from its registers into the other slot
+        // (everybody left that slot before the last barrier); after the barrier those of the second have
+        // the reads of step t + 1's first fragments and the loads of step t + 3 into the registers so
+        // freed.  Every piece is pinned in front of its matrix instruction, as in Pipeline.
+        constexpr int PIECES = A::CHUNKS + B::CHUNKS, GAP = NM / (PIECES > NR ? PIECES : NR);
+        static_assert(GAP >= 2 && KSUB == 2, "every memory instruction of a sub-step needs a slot of its own kind");
         auto step = [&](int t, int slot) __attribute__((always_inline)) {
-            commit(slot ^ 1, slot ^ 1);
-            fetch(t + 3, slot ^ 1);
-            __builtin_amdgcn_sched_barrier(0);  // the loads set out before the matrix instructions
-            PRISM_PARANOID_SYNC(wgp);
-            if (slot == 0 || t < fixed) compute(slot);
+            const int from = t + 3 < fixed ? t + 3 : fixed - 1;  // (as in fetch)
+            const global_bytes a_src = a.step_base(k_begin + from * BK), b_src = b.step_base(k_begin + from * BK);
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                const int piece = m / GAP;
+                if (m % GAP == 0 && piece < NR) read_one(piece, 1, slot, 1);
+                if (m % GAP == 1 && piece < A::CHUNKS) a.commit_one(piece, ra[slot ^ 1], lds + a_slot(slot ^ 1));
+                else if (m % GAP == 1 && piece < PIECES) b.commit_one(piece - A::CHUNKS, rb[slot ^ 1], lds + b_slot(slot ^ 1));
+                __builtin_amdgcn_sched_barrier(0);
+                mfma(m, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
             hand_over();
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                const int piece = m / GAP;
+                if (m % GAP == 0 && piece < NR) read_one(piece, 0, slot ^ 1, 0);
+                if (m % GAP == 1 && piece < A::CHUNKS) a.fetch_one(piece, ra[slot ^ 1], a_src);
+                else if (m % GAP == 1 && piece < PIECES) b.fetch_one(piece - A::CHUNKS, rb[slot ^ 1], b_src);
+                __builtin_amdgcn_sched_barrier(0);
+                mfma(m, 1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            PRISM_PARANOID_SYNC(wgp);
         };
-        for (int t = 0; t < fixed; t += 2) {
+#pragma unroll
+        for (int r = 0; r < NR; ++r) read_one(r, 0, 0, 0);
+        int t = 0;
+        for (; t + 1 < fixed; t += 2) {
             step(t, 0);
             step(t + 1, 1);
         }
+        if (t < fixed) compute(0);
+        __builtin_amdgcn_sched_barrier(0);
     }
 };
 
