@@ -239,7 +239,7 @@ __global__ __launch_bounds__(P::THREADS) void gemm_pipelined(const GemmParams p)
     typename P::tile_t acc;
     acc.clear();
     P::run(wgp, acc, a_tile, a_ld, a_rows, b_tile, b_ld, b_rows,
-           (q.k_end - q.k_begin) / P::K_PER_STEP, lds, wave, lane, p.stamps);
+           (q.k_end - q.k_begin) / P::K_PER_STEP, lds, wave, lane, p.stamps, (q.n0 / BN) & 3, (q.m0 / BM) & 3);
     stamp(p.stamps, STAMP_K_LOOP_DONE);
 
     // The epilogue's per-lane addressing is computed after the K loop: kept live across it, it
@@ -406,18 +406,39 @@ hipError_t launch_pipe(const GemmParams& p, int workgroups, hipStream_t stream)
     return hipGetLastError();
 }
 
+// Operands that the memory-side cache (256 MB) does not hold from call to call, beside C and what else the program
+// touches: their lines are asked for ahead of the copies (Pipeline's AHEAD).  Measured with inputs that change from
+// call to call: 16384 x 4096 x 4096 (168 MB) 378 -> 367 us, 16384 x 10240 x 2048 (109 MB) 484 -> 480,
+// 2048 x 4096 x 16384 (201 MB) 229 -> 210, 1024 x 1024 x 32768 (134 MB) 82 -> 74, row-major B 8192 x 4096 x 8192
+// (201 MB) 375 -> 370; but 4096 x 4096 x 4096 (67 MB) 89.3 -> 90.6, row-major B 8192 x 4096 x 4096 (101 MB) 187 ->
+// 189.  With both operands as k-rows, whose steps lie megabytes apart, earlier: 4096 x 4096 x 4096 107 -> 103,
+// 4096 x 4096 x 8192 with beta 207 -> 203.
+bool operands_from_memory(const GemmParams& p)
+{
+    const double bytes = 2.0 * p.K * (static_cast<double>(p.M) * (p.batch_a == 0 ? 1 : p.batch) + static_cast<double>(p.N) * (p.batch_b == 0 ? 1 : p.batch));
+    return bytes > (p.a_sk != 1 && p.b_sk != 1 ? 6.0e7 : 1.05e8);
+}
+
+template <typename P, typename P_AHEAD>
+hipError_t launch_large(const GemmParams& p, int workgroups, hipStream_t stream)
+{
+    return operands_from_memory(p) ? launch_pipe<P_AHEAD, 256, 256, 64, 2>(p, workgroups, stream) : launch_pipe<P, 256, 256, 64, 2>(p, workgroups, stream);
+}
+template <typename T, bool B_KN, bool A_MK, bool AHEAD = false>
+using Large = wg::Pipeline<T, 256, 256, 64, 2, 2, 2, B_KN, A_MK, AHEAD>;
+
 template <typename T>
 hipError_t launch_pipe_config(int config, const GemmParams& p, int workgroups, hipStream_t stream)
 {
     switch (config) {
-    case 0: return launch_pipe<wg::Pipeline<T, 256, 256, 64, 2, 2, 2>, 256, 256, 64, 2>(p, workgroups, stream);
+    case 0: return launch_large<Large<T, false, false>, Large<T, false, false, true>>(p, workgroups, stream);
     case 1: return launch_pipe<wg::Pipeline<T, 128, 128, 64, 2, 2, 2>, 128, 128, 64, 2>(p, workgroups, stream);
     case 2: return launch_pipe<wg::Pipeline<T, 128, 128, 64, 2, 2, 2, true>, 128, 128, 64, 2>(p, workgroups, stream);
     case 3: return launch_pipe<wg::Pipeline<T, 128, 128, 64, 2, 2, 2, false, true>, 128, 128, 64, 2>(p, workgroups, stream);
     case 4: return launch_pipe<wg::Pipeline<T, 128, 128, 64, 2, 2, 2, true, true>, 128, 128, 64, 2>(p, workgroups, stream);
-    case 9: return launch_pipe<wg::Pipeline<T, 256, 256, 64, 2, 2, 2, true>, 256, 256, 64, 2>(p, workgroups, stream);
-    case 10: return launch_pipe<wg::Pipeline<T, 256, 256, 64, 2, 2, 2, false, true>, 256, 256, 64, 2>(p, workgroups, stream);
-    case 11: return launch_pipe<wg::Pipeline<T, 256, 256, 64, 2, 2, 2, true, true>, 256, 256, 64, 2>(p, workgroups, stream);
+    case 9: return launch_large<Large<T, true, false>, Large<T, true, false, true>>(p, workgroups, stream);
+    case 10: return launch_large<Large<T, false, true>, Large<T, false, true, true>>(p, workgroups, stream);
+    case 11: return launch_large<Large<T, true, true>, Large<T, true, true, true>>(p, workgroups, stream);
     default: return hipErrorInvalidValue;
     }
 }

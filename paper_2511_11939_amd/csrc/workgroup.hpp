@@ -82,6 +82,15 @@ __device__ __forceinline__ void copy_async_16(persp::Wave, const char* uniform_b
                  : "memory", "scc");
 }
 
+// Asks for the 128-byte lines that hold the lanes' bytes, so that they are in the die's L2 when their copies are
+// issued: one word per lane, dropped at `lds_sink` (256 bytes nobody reads).
+__device__ __forceinline__ void touch_lines(persp::Wave, const char* uniform_base, uint32_t lane_offset, uint32_t lds_sink)
+{
+    uniform_base = scalarize(uniform_base);
+    lds_sink = __builtin_amdgcn_readfirstlane(lds_sink);
+    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dword %0, %1" : : "v"(lane_offset), "s"(uniform_base), "s"(lds_sink) : "memory");
+}
+
 // ---- from the accumulators to memory ---------------------------------------------------
 // Every lane holds four consecutive columns of one row per block: row 16 i + lane % 16 of the
 // wave tile, columns lane::acc_first_col<PAIRED>(j, lane) and on.  Two ways out:
@@ -168,7 +177,7 @@ __device__ __forceinline__ void drain_rows(persp::Wave wv, const TileT& acc, cha
 // copied as it lies in memory, and the fragments, which need consecutive k per lane, are
 // fetched with the transposing LDS read of gfx950, two per fragment).
 // ------------------------------------------------------------------------------------
-template <typename T, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, bool B_KN = false, bool A_MK = false>
+template <typename T, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, bool B_KN = false, bool A_MK = false, bool AHEAD = false>
 struct Pipeline {
     using L = lane::TileLayout<BK>;
     static constexpr int ES = Frag<T>::kElemBytes;
@@ -189,7 +198,8 @@ struct Pipeline {
     static constexpr int KSUB = BK / lane::kBlockK;
     static constexpr int A_BYTES = BM * L::kRowBytes, B_BYTES = BN * L::kRowBytes;
     static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
-    static constexpr int LDS_BYTES = STAGES * STAGE_BYTES;
+    static constexpr int SINK_BYTES = AHEAD ? NW * 256 : 0;  // where touched lines go, behind the slots
+    static constexpr int LDS_BYTES = STAGES * STAGE_BYTES + SINK_BYTES;
     // LDS: the A tiles of all slots first, then the B tiles.  A lane's fragment addresses are then
     // one base per operand and sub-step plus constants below 64 KiB (block, slot), which fit the
     // offset field of the LDS read: no address arithmetic inside the K loop.
@@ -224,7 +234,7 @@ struct Pipeline {
     // has the next MFMA queued while the memory instructions issue.
     __device__ __forceinline__ static void run(persp::Workgroup wgp, tile_t& acc, const char* a_tile, uint32_t a_ld, int a_rows,
                                const char* b_tile, uint32_t b_ld, int b_rows, int ksteps,
-                               char* lds, int wave, int lane, uint64_t* stamps = nullptr)
+                               char* lds, int wave, int lane, uint64_t* stamps = nullptr, int a_share = 0, int b_share = 0)
     {
         const persp::Wave wv = wgp.wave();  // every wave of the workgroup runs this code
         constexpr int PARTS = wave::mfma_parts(frag_t{});  // matrix instructions per block and sub-step
@@ -290,6 +300,35 @@ struct Pipeline {
             if (__builtin_constant_p(stage)) copy_async_16(wv, src, g_off[c], lds0, slot + in_slot);
             else copy_async_16(wv, src, g_off[c], lds0 + slot, in_slot);
         };
+        // AHEAD: the lines of a K step are asked for one step before its copies, so that a copy from memory has
+        // two steps to arrive.  The two slots alone leave one: 4 MiB of different lines on their way in the
+        // whole chip where 256 workgroups share their panels by fours, half of what memory's latency takes to
+        // keep up 5 TB/s.  The workgroups of a die that share a panel share the asking: each asks for a
+        // quarter of its rows of A (waves 0 and 1, every row by two lanes) and of B.  Measured with operands from
+        // memory: 1024 x 1024 x 32768 in slices 82.3 -> 74.1 us, 2048 x 4096 x 16384 233.6 -> 215.5; half of the rows,
+        // or two steps earlier, is no better.  Where the caches hold the operands the lines only cost power:
+        // 4096 x 4096 x 4096 89.3 -> 90.6.
+        uint32_t touch_off = 0;
+        const char* touch_tile = wave < NW / 2 ? a_tile : b_tile;
+        const uint32_t sink = lds_address(lds) + STAGES * STAGE_BYTES + wave * 256;
+        int64_t touch_step = L::kRowBytes;
+        if constexpr (AHEAD) {
+            static_assert(BM == 256 && BN == 256 && NW == 4 && ES == 2, "a quarter of a panel's lines by two waves");
+            const bool of_a = wave < 2, k_rows = of_a ? A_MK : B_KN;
+            const int share = of_a ? a_share : b_share, exist = of_a ? a_rows : b_rows;
+            const uint32_t ld = of_a ? a_ld : b_ld;
+            if (k_rows) {  // sixteen k-rows of four lines
+                const int k_row = share * 16 + (wave & 1) * 8 + (lane & 31) / 4, byte = (lane & 3) * 128;
+                touch_off = __umul24(static_cast<uint32_t>(k_row), ld) + (byte < exist * ES ? byte : 0);
+                touch_step = static_cast<int64_t>(K_PER_STEP) * ld;
+            } else {
+                const int row = share * 64 + (wave & 1) * 32 + (lane & 31);
+                touch_off = __umul24(static_cast<uint32_t>(row < exist ? row : exist - 1), ld);
+            }
+        }
+        auto touch = [&](int step) __attribute__((always_inline)) {
+            touch_lines(wv, touch_tile + (step < ksteps ? step : ksteps - 1) * touch_step, touch_off, sink);
+        };
         // -- prologue, first part: fill the slots.  The copies go out before the addressing of the
         //    fragment reads is worked out: that arithmetic then runs while the first bytes travel.
 #pragma unroll
@@ -298,6 +337,7 @@ struct Pipeline {
 #pragma unroll
                 for (int c = 0; c < COPIES; ++c) copy(c, s, s);
             }
+        if constexpr (AHEAD) touch(STAGES);
         __builtin_amdgcn_sched_barrier(0);
 
         // fp32 fragment from k-rows: element e of lane (x, g) is the value at k-row 16*ksub + 4g + e,
@@ -372,8 +412,8 @@ struct Pipeline {
         };
 
         // -- prologue, second part: wait for step 0, fetch its first fragments
-        if (ksteps >= STAGES) wait_counts<(STAGES - 1) * COPIES, 0>();
-        else wait_counts<0, 0>();
+        if (ksteps >= STAGES) wait_counts<(STAGES - 1) * COPIES + (AHEAD ? 1 : 0), 0>();
+        else wait_counts<AHEAD ? 1 : 0, 0>();
         barrier(wgp);
         asm volatile("" ::: "memory");
 #pragma unroll
@@ -423,7 +463,8 @@ struct Pipeline {
                 } else if (!LAST) {
                     // Hand-over: my copies for step t+1 have landed and my reads of this
                     // slot are done; after the barrier that holds for every wave.
-                    wait_counts<0, 0>();
+                    // (lines asked for after those copies may still be on their way, see AHEAD)
+                    wait_counts<AHEAD ? 1 : 0, 0>();
                     barrier(wgp);
                     asm volatile("" ::: "memory");  // keep what follows on this side of the barrier
                     __builtin_amdgcn_sched_barrier(0);
@@ -431,6 +472,7 @@ struct Pipeline {
                     for (int m = 0; m < NM; ++m) {
                         if (m % READ_SPACING == 0 && m / READ_SPACING < NR) read(m / READ_SPACING, nxt, next, 0);
                         if (TAIL && m % TAIL_SPACING == 1 && m / TAIL_SPACING < TAILN) copy(m / TAIL_SPACING, t + 2, stage);
+                        if (AHEAD && m == NM - 1) touch(t + 3);
                         __builtin_amdgcn_sched_barrier(0);  // memory instructions stay in front of their MFMA
                         mfma(m, cur);
                         __builtin_amdgcn_sched_barrier(0);
@@ -486,7 +528,7 @@ struct Pipeline {
                     else if (x < KSUB) toggle(fb_off[x]);
                 }
                 const int after_next = (t + 2 < ksteps ? t + 2 : ksteps - 1), stage = t & 1;
-                wait_counts<0, 0>();
+                wait_counts<AHEAD ? 1 : 0, 0>();
                 barrier(wgp);
                 asm volatile("" ::: "memory");
                 __builtin_amdgcn_sched_barrier(0);
@@ -494,6 +536,7 @@ struct Pipeline {
                 for (int m = 0; m < NM; ++m) {
                     if (m % READ_SPACING == 0 && m / READ_SPACING < NR) read(m / READ_SPACING, 0, 0, 0);
                     if (m % TAIL_SPACING == 1 && m / TAIL_SPACING < COPIES) copy(m / TAIL_SPACING, after_next, stage);
+                    if (AHEAD && m == NM - 1) touch(t + 3);
                     __builtin_amdgcn_sched_barrier(0);
                     mfma(m, 1);
                     __builtin_amdgcn_sched_barrier(0);
@@ -507,6 +550,7 @@ struct Pipeline {
         }
         if (ksteps == 1) {
             k_step(no{}, no{}, yes{}, 0, 0, 0);
+            if constexpr (AHEAD) wait_counts<0, 0>();
             __builtin_amdgcn_sched_barrier(0);
             return;
         }
@@ -527,6 +571,7 @@ struct Pipeline {
             ++t;
         }
         k_step(no{}, no{}, yes{}, t, t & 1, t & 1);
+        if constexpr (AHEAD) wait_counts<0, 0>();  // the lines asked for past the end
         __builtin_amdgcn_sched_barrier(0);  // nothing of the epilogue moves up into the K loop
     }
 };
