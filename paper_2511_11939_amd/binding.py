@@ -11,6 +11,7 @@ from typing import Optional
 from . import build as _build
 
 _lib = None
+_call = None  # the native way of the usual call, once bound
 
 
 class Status(enum.IntEnum):
@@ -78,8 +79,8 @@ def load_library():
     global _lib
     if _lib is not None:
         return _lib
-    if not os.path.exists(_build.LIB_PATH):
-        _build.build()
+    if not os.path.exists(_build.LIB_PATH) or not os.path.exists(_build.CALL_PATH):
+        _build.build(force=True)
     elif _build.is_stale():
         import warnings
         warnings.warn("libprism_gemm.so is older than its sources: run paper_2511_11939_amd.build.build(force=True)")
@@ -252,11 +253,34 @@ def _stream(stream) -> int:
     return _current_stream()
 
 
+def _bind_call():
+    """Binds the native way of the usual call, which gemm and scan_u32 use from then on, to the loaded
+    library and to torch.  The first question for a device initialises the GPU, as _stream's does."""
+    global _call
+    import torch
+    from . import _call as native
+    torch.cuda.current_device()
+    raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw_stream is None:
+        raw_stream = lambda device: torch.cuda.current_stream(device).cuda_stream  # noqa: E731
+    lib = load_library()
+    address = [ctypes.cast(f, ctypes.c_void_p).value for f in (lib.prism_gemm, lib.prism_gemm_batched, lib.prism_scan_u32)]
+    native.bind(*address, GemmDesc, torch._C._cuda_getDevice, raw_stream)
+    _call = native
+    return native
+
+
 def gemm(A, B, C, *, M, N, K, desc: GemmDesc, lda=None, ldb=None, ldc=None, batch=1,
          strideA=None, strideB=None, strideC=None, stream=None):
     """Enqueue C <- alpha*A*B + bias + beta*C on `stream` (a torch.cuda.Stream, a raw
     hipStream_t value or None for torch's current stream).  A, B, C: device tensors or
     raw device pointers, laid out as `desc` says.  Raises PrismError on a bad status."""
+    if stream is None:
+        s = (_call or _bind_call()).gemm(A, B, C, M, N, K, desc, lda, ldb, ldc, batch, strideA, strideB, strideC)
+        if s == 0:
+            return
+        if s is not None:
+            raise PrismError(s, "prism_gemm")
     if lda is None:
         lda = (K if desc.layout_a == _ROW else M) or 1
     if ldb is None:
@@ -265,11 +289,7 @@ def gemm(A, B, C, *, M, N, K, desc: GemmDesc, lda=None, ldb=None, ldc=None, batc
         ldc = (N if desc.layout_c == _ROW else M) or 1
     lib = _lib or load_library()
     single = batch == 1 and strideA is None and strideB is None and strideC is None
-    # (the pointers of the usual case, three tensors, without the questions that _p asks)
-    try:
-        A, B, C = A.data_ptr(), B.data_ptr(), C.data_ptr()
-    except AttributeError:
-        A, B, C = _p(A), _p(B), _p(C)
+    A, B, C = _p(A), _p(B), _p(C)
     if single:
         s = lib.prism_gemm(_descp(desc), M, N, K, A, max(lda, 1), B, max(ldb, 1), C, max(ldc, 1), _stream(stream))
     else:
@@ -306,6 +326,12 @@ def scan_u32(inp, out, n, workspace, *, stream=None):
     """Enqueue the inclusive uint32 prefix sum of `inp` into `out` (may be the same tensor) on
     `stream` (torch stream, raw hipStream_t or None for torch's current stream).  `workspace`:
     a device tensor of at least prism_scan_workspace_size(n) bytes.  Raises on a bad status."""
+    if stream is None:
+        s = (_call or _bind_call()).scan(inp, out, n, workspace)
+        if s == 0:
+            return
+        if s is not None:
+            raise PrismError(s, "prism_scan_u32")
     nbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     lib = _lib or load_library()
     s = lib.prism_scan_u32(_p(inp), _p(out), n, _p(workspace), nbytes, _stream(stream))

@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -13,6 +14,8 @@ LIB_PATH = os.path.join(_HERE, "libprism_gemm.so")
 # where the lanes of one wave pass data through LDS (race check: its results must equal the normal
 # build's bit for bit)
 PARANOID_LIB_PATH = os.path.join(_HERE, "libprism_gemm_paranoid.so")
+# the usual call from Python, without ctypes (a module of this package, for the interpreter that builds it)
+CALL_PATH = os.path.join(_HERE, "_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 _UNITS = ["kernels.hip", "skinny.hip", "dealt.hip", "host_api.hip", "scan.hip", "probe.hip"]
 _PARANOID_UNITS = ["kernels.hip", "skinny.hip", "dealt.hip"]  # the units that have such phases
 _FLAGS = [
@@ -31,9 +34,10 @@ def _sources():
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB_PATH) or not os.path.exists(PARANOID_LIB_PATH):
+    built = (LIB_PATH, PARANOID_LIB_PATH, CALL_PATH)
+    if not all(os.path.exists(p) for p in built):
         return True
-    t = min(os.path.getmtime(LIB_PATH), os.path.getmtime(PARANOID_LIB_PATH))
+    t = min(os.path.getmtime(p) for p in built)
     return any(os.path.getmtime(s) > t for s in _sources())
 
 
@@ -57,9 +61,18 @@ def build(force: bool = False, verbose: bool = False) -> str:
         if "warning:" in r.stderr:
             print(r.stderr, file=sys.stderr, flush=True)
 
+    def compile_call(_):
+        cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-Wall",
+               "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "call.cpp"), "-o", CALL_PATH]
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        if r.returncode != 0:
+            raise RuntimeError(f"call.cpp: {r.stdout}\n{r.stderr}")
+
     jobs = [(u, False) for u in _UNITS] + [(u, True) for u in _PARANOID_UNITS]
-    with ThreadPoolExecutor(max_workers=len(jobs)) as ex:
+    with ThreadPoolExecutor(max_workers=len(jobs) + 1) as ex:
+        call = ex.submit(compile_call, None)
         list(ex.map(compile_one, jobs))
+        call.result()
     for lib, paranoid in ((LIB_PATH, False), (PARANOID_LIB_PATH, True)):
         these = [obj(u, paranoid and u in _PARANOID_UNITS) for u in _UNITS]
         cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *these, "-o", lib]
