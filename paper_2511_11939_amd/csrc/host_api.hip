@@ -370,8 +370,19 @@ prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, in
     // least a chunk; chosen over tiles further down.  Not for more than 32 rows where 128x128 tiles give
     // half of the compute units a workgroup, because every 16 or 32 columns read all rows of A again
     // (64 x 16384 x 4096: 39.2 us with tiles, 41.3 without; 128 problems of 64 x 512 x 512: 24.4 and 38.6).
-    // Two blocks of columns where that still gives every compute unit a workgroup.
-    const int64_t skinny_m = p.M <= 16 ? 16 : p.M <= 32 ? 32 : 64, skinny_n = ceil_div(p.N, 32) * batch >= kComputeUnits ? 32 : 16;
+    // Two blocks of columns where that still gives every compute unit a workgroup, and where the last round of
+    // workgroups is not much emptier than with one (16 x 8400 x 4096, 263 workgroups or 525: 20.8 -> 15.8 us;
+    // 5 x 8223 x 10880 49.2 -> 40.5, 4 x 18000 x 4096 35.3 -> 29.1).  More than 16 rows pay for one block with half as
+    // many loads again: only where B is what counts (30 x 9000 x 4096 21.4 -> 19.8, but 28 x 8500 x 1280 8.9 -> 10.8).
+    const int64_t skinny_m = p.M <= 16 ? 16 : p.M <= 32 ? 32 : 64;
+    const auto last_round = [](int64_t workgroups) {
+        return static_cast<double>(workgroups) / static_cast<double>(ceil_div(workgroups, kComputeUnits) * kComputeUnits);
+    };
+    const int64_t one_block = ceil_div(p.N, 16) * batch, two_blocks = ceil_div(p.N, 32) * batch;
+    const double b_bytes = static_cast<double>(ab_esize) * static_cast<double>(p.N) * static_cast<double>(K) * static_cast<double>(p.batch_b == 0 ? 1 : batch);
+    const bool uneven = last_round(one_block) > 1.15 * last_round(two_blocks) && (p.M <= 16 || b_bytes > 4.8e7) &&
+                        !prism::few_rows_stream_b(p.N, K, ab_esize, batch, p.batch_b);
+    const int64_t skinny_n = two_blocks >= kComputeUnits && !uneven ? 32 : 16;
     const int64_t skinny_workgroups = ceil_div(p.N, skinny_n) * batch;
     // as many waves as have K steps of their own, sixteen only where workgroups are few
     const int skinny_waves = ksteps >= 32 && skinny_workgroups <= kComputeUnits / 2 ? 16 : ksteps >= 8 ? 8 : 4;
