@@ -92,8 +92,8 @@ typedef struct prism_gemm_plan {
                                     whole sums per workgroup, no tile loop, no split;
                                 with 1 and 2 and tile_n below 128 the waves of a
                                 workgroup deal K steps among themselves              */
-    int32_t tile_m, tile_n, tile_k; /* workgroup tile; 128 x 32 x tile_k: of four workgroups
-                                    of 32 rows each                                  */
+    int32_t tile_m, tile_n, tile_k; /* workgroup tile; 128 x 32: of four workgroups of 32
+                                    rows each, 128 x 64: of one, or of two of 64     */
     int32_t waves;           /* wavefronts per workgroup                              */
     int32_t split_k;         /* K slices actually used (>= 1)                         */
     int32_t swapped;         /* 1 if the problem is run as C^T = B^T A^T              */

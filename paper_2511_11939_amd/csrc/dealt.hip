@@ -7,14 +7,14 @@
 // it computes the present one, passes the step through LDS of its own (from the order of whole rows into
 // the matrix instruction's), and no barrier stands in the loop.  At the end the waves' sums are added in wave order, so
 // the result does not depend on timing.  32 x 32 results per workgroup of four or eight waves fill the chip
-// from a quarter of a million results on; 128 x 64 by eight waves (two halves of 64 rows, four
-// waves along K each) take half the loads per result and serve larger products.  From there on the loads
+// from a quarter of a million results on; 64 x 64 by eight waves, and 128 x 64 by eight (two halves of 64 rows,
+// four waves along K each), take half the loads per result and serve larger products.  From there on the loads
 // bind, 64 bytes a clock per compute unit, at a quarter and at half of the matrix rate, and tiles are
 // faster: the host predicts both.  Measured (whole call, tiles before): 704 x 704 x 1856 row-major B
 // 19.7 -> 9.5 us, 157 x 1353 x 384 10.0 -> 5.2, 183 x 512 x 1241 21.8 -> 5.3, 265 x 1344 x 768 fp32 58.6 -> 11.7,
 // 64 x 192 x 20352 in slices 16.6 -> 9.3, 256 x 256 x 256 row-major B 5.6 -> 5.2.  Tried and
-// not kept: 64 x 32, 64 x 64 and 128 x 32 results per workgroup and sixteen waves (best for one product in ten, by
-// one percent over all of them).
+// not kept: 64 x 32 and 128 x 32 results per workgroup, 64 x 64 by four waves, and sixteen waves (best for one product
+// in ten, by half a percent over all of them).
 //
 // Rows that start in the middle of a 32-bit word (16-bit operands, odd pitches): the vector memory unit takes
 // such a 16-byte load in pieces (38 bytes a ns and compute unit against 110 for loads at whole
@@ -345,6 +345,7 @@ template <typename T>
 hipError_t launch_typed(int rows, int waves, bool odd_rows, const GemmParams& p, int workgroups, hipStream_t stream)
 {
     if (rows == 128) launch_layout<T, 4, 4, 2, 4>(odd_rows, p, workgroups, stream);
+    else if (rows == 64) launch_layout<T, 4, 4, 1, 8>(odd_rows, p, workgroups, stream);
     else if (waves == 8) launch_layout<T, 2, 2, 1, 8>(odd_rows, p, workgroups, stream);
     else launch_layout<T, 2, 2, 1, 4>(odd_rows, p, workgroups, stream);
     return hipGetLastError();

@@ -206,7 +206,7 @@ double tiles_us(const TileTimes& t, bool large, int64_t workgroups, const Slices
 // kDealtMargin, more for calls of several rounds and for long rows of both operands, whose loads
 // touch many pages; and operands beyond what the memory-side cache holds from call to call stay on
 // tiles.  Measured over all of them, the calls take 0.69 of the time that tiles alone take (the
-// best choice each time: 0.66), and 24 are more than 5 % slower (the worst 32 %).
+// best choice each time: 0.66), and 25 are more than 5 % slower (the worst 32 %).
 struct DealtTimes {
     double first, round;      // us: a call of one round of workgroups, and each further round
     double step;              // us of a wave's K step
@@ -216,14 +216,16 @@ struct DealtTimes {
 };
 struct DealtShape {
     int rows, columns, waves, waves_m, resident;  // of a workgroup; waves side by side along m; workgroups of a compute unit
-    int split_workgroups;                         // of all units together, up to which sums are split
+    int split_workgroups;                         // of all units together, up to which sums are split (0: never)
     DealtTimes times[3];                          // by kind of operands, as above
 };
-constexpr DealtShape kDealtShapes[3] = {
+constexpr DealtShape kDealtShapes[4] = {
     {32, 32, 4, 1, 5, 2 * kComputeUnits,
      {{3.4, 2.3, 0.05, 81.3, 0.29, 4.0, 3.3, 0.05}, {3.8, 2.8, 0.01, 65.4, 0.27, 3.4, 4.8, 0.01}, {3.9, 3.1, 0.01, 52.5, 0.02, 4.0, 4.2, 0.01}}},
     {32, 32, 8, 1, 2, 2 * kComputeUnits,
      {{3.0, 1.8, 0.59, 90.7, 0.36, 4.1, 3.4, 0.16}, {3.3, 2.0, 0.82, 68.0, 0.27, 5.3, 5.3, 0.01}, {3.8, 2.6, 0.27, 60.1, 0.04, 3.1, 4.3, 0.12}}},
+    {64, 64, 8, 1, 1, 0,
+     {{4.6, 3.6, 0.09, 83.4, 0.09, 3.4, 3.2, 0.24}, {5.0, 4.1, 0.49, 66.9, 0.10, 3.0, 4.6, 0.07}, {5.6, 4.6, 0.04, 33.6, 0.01, 3.5, 4.5, 0.39}}},
     {128, 64, 8, 2, 1, kComputeUnits,
      {{5.1, 4.3, 0.01, 92.6, 0.08, 2.9, 2.6, 0.26}, {5.7, 4.9, 0.01, 71.0, 0.05, 2.7, 3.6, 0.17}, {5.5, 4.6, 1.67, 34.1, 0.01, 2.0, 4.3, 0.34}}},
 };
@@ -385,7 +387,11 @@ prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, in
     const int64_t skinny_n = two_blocks >= kComputeUnits && !uneven ? 32 : 16;
     const int64_t skinny_workgroups = ceil_div(p.N, skinny_n) * batch;
     // as many waves as have K steps of their own, sixteen only where workgroups are few
-    const int skinny_waves = ksteps >= 32 && skinny_workgroups <= kComputeUnits / 2 ? 16 : ksteps >= 8 ? 8 : 4;
+    // (and up to one per compute unit where that leaves four to eight whole steps to a wave, all of them on their way at
+    // once: 16 x 4096 x 4096 8.6 -> 8.2 us, 8 x 2500 x 8192 11.1 -> 10.6; but 16 x 4096 x 2048 5.6 -> 6.2,
+    // 5 x 4000 x 16384 28.4 -> 29.1, 60 x 4096 x 4096 11.6 -> 12.2, and 7 x 3967 x 4801, whose rest comes last, 10.6 -> 12.0)
+    const bool four_to_eight = ksteps >= 64 && ksteps <= 128 && K % step_k == 0 && skinny_m <= 32 && skinny_n == 16 && skinny_workgroups <= kComputeUnits;
+    const int skinny_waves = ksteps >= 32 && (skinny_workgroups <= kComputeUnits / 2 || four_to_eight) ? 16 : ksteps >= 8 ? 8 : 4;
     const bool many_tiles = p.M > 32 && pipe_ok && ceil_div(p.N, prism::kStagedTileN) * batch >= kComputeUnits / 2;
     const bool few_rows = allow_few_rows && p.M <= kSkinnyRows && a_kfast && b_kfast && K >= epc && pitch_ok && d->split_k <= 1 &&
                           hk.pipe_config < 0 && hk.persistent != 1 && skinny_workgroups <= kSkinnyMaxWorkgroups && !many_tiles;
@@ -515,7 +521,8 @@ prism_status_t make_problem(const prism_gemm_desc_t* d, int64_t M, int64_t N, in
             }
         }
         if (chosen) {
-            // The schedule deals blocks of four 32-row tiles, one below the other, to neighbouring workgroups.
+            // The schedule deals blocks of four tile rows, one below the other, to neighbouring workgroups: 128 rows
+            // are a block of four, two or one.
             plan.tile_m = 128;
             plan.tile_n = chosen->columns;
             plan.tile_k = static_cast<int32_t>(step_k);

@@ -37,7 +37,7 @@ constexpr bool few_rows_stream_b(int64_t N, int64_t K, int esize, int64_t batch,
     return static_cast<double>(N) * static_cast<double>(K) * esize * static_cast<double>(batch_b == 0 ? 1 : batch) > 268435456.0;
 }
 hipError_t launch_skinny(int ab_dtype, int tile_m, int tile_n, int waves, const GemmParams& p, int workgroups, hipStream_t stream);
-// K steps dealt to the waves of a workgroup: `rows` (32 or 128) rows of C by 32 or 64 columns, 4 or 8 waves; odd_rows:
+// K steps dealt to the waves of a workgroup: `rows` of C (32, by 32 columns and 4 or 8 waves; 64 or 128, by 64 columns and 8 waves); odd_rows:
 // 16-bit operands some of whose rows start in the middle of a 32-bit word, all in words of the operand.
 hipError_t launch_dealt(int ab_dtype, int rows, int waves, bool odd_rows, const GemmParams& p, int workgroups, hipStream_t stream);
 // Sums the split_k partial slabs in slice order and applies the epilogue; with

@@ -82,3 +82,12 @@ def test_race_check_build(paranoid, la, lb, ab, M, N, K):  # noqa: F811
         torch.cuda.synchronize()
         outs.append(C)
     assert not outs[0].isnan().any() and torch.equal(outs[0].view(torch.int32), outs[1].view(torch.int32))
+
+
+@pytest.mark.parametrize("la,lb", LAYOUTS)
+@pytest.mark.parametrize("M,N,K", [(960, 904, 1088), (961, 903, 1087)])
+def test_workgroups_of_64_rows(la, lb, M, N, K):
+    plan = _plan(M, N, K, la, lb)
+    assert _dealt(plan) and plan.tile_n == 64 and plan.workgroups == -(-M // 64) * -(-N // 64)
+    _general_case(M, N, K, la=la, lb=lb, ab="f16", cd="f16", ints=True)
+    _general_case(M, N, K, la=la, lb=lb, lc="col", pad=(1, 1, 3), bias=True, alpha=-0.5, beta=0.25)
