@@ -53,11 +53,11 @@ def source_digest() -> str:
 # (two runs), each divided by the factor the same counter shows on a copy of known size
 # (--calibrate-copy).  Summaries under profiles/.  workload -> (bytes, digest of the sources).
 MEASURED_TRAFFIC: dict = {
-    "cfg2_4096_bf16": (235348298, "74b233054672067b"),
-    "cfg3_proj_bias": (940398335, "74b233054672067b"),
-    "cfg4_splitk_f16": (273119068, "74b233054672067b"),   # main kernel + reduction
-    "cfg5_batched_512": (403148969, "74b233054672067b"),
-    "scan_u32_2p28": (2157279709, "74b233054672067b"),
+    "cfg2_4096_bf16": (235342559, "6eeae35b3f8ca399"),
+    "cfg3_proj_bias": (940300504, "6eeae35b3f8ca399"),
+    "cfg4_splitk_f16": (273344741, "6eeae35b3f8ca399"),   # main kernel + reduction
+    "cfg5_batched_512": (403165672, "6eeae35b3f8ca399"),
+    "scan_u32_2p28": (2157262389, "6eeae35b3f8ca399"),
 }
 
 
